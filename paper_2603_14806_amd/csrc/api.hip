@@ -298,22 +298,27 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
         e = trimul::launch_contract(h->dtype, 1, dCp, B, dA, N, N, N, 0, 0, N, 0, 0, N * N, h->c, 0, nullptr, cus, s);
     if (e == hipSuccess) e = trimul::launch_contract_transposed(1, 0, dCp, A, dB, N, N, N, h->c, cus, s);
     if (e == hipSuccess) e = trimul::launch_projection_backward(h->w, z, mask, N, incoming, dA, dB, dxg, dz, bb, ppb, G, s);
-    const struct { const bf16_t* u; const bf16_t* v; float* out; } wg[] = {{bb.du, bb.y, g->w_o}, {bb.dgg, bb.xe, g->w_g}};
-    for (const auto& q : wg) {
-        if (e == hipSuccess) e = trimul::launch_wgrad(q.u, q.v, N, pw, GW, s);
-        if (e == hipSuccess) e = trimul::launch_sum_parts(pw, GW, 128 * 128, 128 * 128, q.out, s);
-    }
+    constexpr int kW = 128 * 128;
+    if (e == hipSuccess) e = trimul::launch_wgrad(bb.du, bb.y, N, pw, GW, s);
+    const trimul::SumTask sum_wo{pw, g->w_o, GW, kW, kW, 0};
+    if (e == hipSuccess) e = trimul::launch_sum_parts(&sum_wo, 1, s);
+    if (e == hipSuccess) e = trimul::launch_wgrad(bb.dgg, bb.xe, N, pw, GW, s);
     // the four projection weights share the x blocks: one pass over them
     const bf16_t* const u4[4] = {bb.dpa, bb.dga, bb.dpb, bb.dgb};
-    float* const out4[4] = {g->w_a, g->w_ga, g->w_b, g->w_gb};
     if (e == hipSuccess) e = trimul::launch_wgrad4(u4, bb.xp, N, pw4, GW4, s);
-    for (int o = 0; o < 4; ++o)
-        if (e == hipSuccess)
-            e = trimul::launch_sum_parts(pw4 + (size_t)o * GW4 * 128 * 128, GW4, 128 * 128, 128 * 128, out4[o], s);
-    if (e == hipSuccess) e = trimul::launch_sum_parts(peb, G, 256, 128, g->ln_out_w, s);
-    if (e == hipSuccess) e = trimul::launch_sum_parts(peb + 128, G, 256, 128, g->ln_out_b, s);
-    if (e == hipSuccess) e = trimul::launch_sum_parts(ppb, G, 256, 128, g->ln_in_w, s);
-    if (e == hipSuccess) e = trimul::launch_sum_parts(ppb + 128, G, 256, 128, g->ln_in_b, s);
+    const size_t p4 = (size_t)GW4 * kW;
+    const trimul::SumTask sums[] = {
+        {pw, g->w_g, GW, kW, kW, 0},
+        {pw4, g->w_a, GW4, kW, kW, 0},
+        {pw4 + p4, g->w_ga, GW4, kW, kW, 0},
+        {pw4 + 2 * p4, g->w_b, GW4, kW, kW, 0},
+        {pw4 + 3 * p4, g->w_gb, GW4, kW, kW, 0},
+        {peb, g->ln_out_w, G, 256, 128, 0},
+        {peb + 128, g->ln_out_b, G, 256, 128, 0},
+        {ppb, g->ln_in_w, G, 256, 128, 0},
+        {ppb + 128, g->ln_in_b, G, 256, 128, 0},
+    };
+    if (e == hipSuccess) e = trimul::launch_sum_parts(sums, 9, s);
     if (e != hipSuccess) return hip_fail(e, "backward kernel launch");
     return ok();
 }

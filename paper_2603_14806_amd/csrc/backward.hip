@@ -840,7 +840,6 @@ __global__ __launch_bounds__(256) void k_wgrad(const bf16_t* __restrict__ U, con
         for (int r = 0; r < 16; ++r) pw[(32 * w + 8 * (r >> 2) + 4 * hi + (r & 3)) * kCh + 32 * j + rl] = acc[j][r];
 }
 
-// out[i] = sum over g < parts of in[g * stride + i], in that order.
 // Four weight gradients that share their second operand (W_a, W_ga, W_b,
 // W_gb all multiply the x blocks): sum over units of U_o V^T for o = 0..3,
 // reading each unit's V block once instead of four times.  8 waves: wave w
@@ -903,13 +902,41 @@ __global__ __launch_bounds__(512) void k_wgrad4(Wgrad4Args a, const bf16_t* __re
     }
 }
 
-__global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ in, int parts, int64_t stride, int n,
-                                                    float* __restrict__ out) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-    for (int g = 0; g < parts; ++g) s += in[(int64_t)g * stride + i];
-    out[i] = s;
+// Sums of the per-work-group partials: out[i] = sum over g < parts of
+// in[g * stride + i], for several outputs in one launch.  A work-group takes
+// 32 consecutive outputs of one sum (one 128-byte line of every partial): 32
+// slices of 8 lanes each add every 32nd partial, then the slices are added in
+// order, so the result does not depend on the grid and is the same every
+// time.  Bound by the latency of reading the partials (16 MB for one 128 x
+// 128 gradient): one thread per output, which walked all of them alone, kept
+// 64 work-groups on a serial chain of 256 to 512 loads, 96 us a sum and
+// 870 us of a backward call; now the two launches of a call take 26 us
+// (N = 384, 256 compute units).
+__global__ __launch_bounds__(256) void k_sum_parts(SumTasks a) {
+    __shared__ __align__(16) float4 red[32][8];
+    int i = 0;
+    while (i + 1 < a.count && (int)blockIdx.x >= a.task[i + 1].block0) ++i;
+    const SumTask q = a.task[i];
+    const int t = threadIdx.x, lane = t & 7, slice = t >> 3;
+    const float* p = q.in + 32 * ((int)blockIdx.x - q.block0) + 4 * lane;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int g = slice; g < q.parts; g += 32) {
+        const float4 v = *reinterpret_cast<const float4*>(p + (int64_t)g * q.stride);
+        s.x += v.x;
+        s.y += v.y;
+        s.z += v.z;
+        s.w += v.w;
+    }
+    red[slice][lane] = s;
+    __syncthreads();
+    if (t < 32) {
+        const float* r = reinterpret_cast<const float*>(red) + t;
+        float o = 0.f;
+#pragma unroll
+        for (int g = 0; g < 32; ++g) o += r[32 * g];
+        q.out[32 * ((int)blockIdx.x - q.block0) + t] = o;
+    }
 }
 
 }  // namespace
@@ -990,8 +1017,16 @@ hipError_t launch_wgrad4(const bf16_t* const U[4], const bf16_t* V, int64_t N, f
     return hipGetLastError();
 }
 
-hipError_t launch_sum_parts(const float* in, int parts, int64_t stride, int n, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, parts, stride, n, out);
+hipError_t launch_sum_parts(const SumTask* tasks, int count, hipStream_t s) {
+    SumTasks a;
+    a.count = count;
+    int blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        a.task[i] = tasks[i];
+        a.task[i].block0 = blocks;
+        blocks += tasks[i].n / 32;
+    }
+    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -151,7 +151,19 @@ hipError_t launch_wgrad(const bf16_t* U, const bf16_t* V, int64_t N, float* part
 // Four weight gradients sharing V: partial[o][grid][128][128] for U[o] V^T, o = 0..3.
 hipError_t launch_wgrad4(const bf16_t* const U[4], const bf16_t* V, int64_t N, float* partial, int grid,
                          hipStream_t s);
-hipError_t launch_sum_parts(const float* in, int parts, int64_t stride, int n, float* out, hipStream_t s);
+// Sums of partials, several in one launch: out[i] = sum over g < parts of in[g * stride + i], i < n (n a
+// multiple of 32; in and stride 16-byte aligned).  block0 is filled in by the launcher.
+struct SumTask {
+    const float* in;
+    float* out;
+    int parts, stride, n, block0;
+};
+constexpr int kMaxSumTasks = 10;
+struct SumTasks {
+    SumTask task[kMaxSumTasks];
+    int count;
+};
+hipError_t launch_sum_parts(const SumTask* tasks, int count, hipStream_t s);
 
 // Outer product mean (opm.hip).  Pack: tokens [tok0, tok0 + ntok) and
 // sequences [s0, s0 + slen) of a [S][n_total][32] bf16 tensor, masked, into
