@@ -389,30 +389,32 @@ int tri_mul_init(tri_mul_handle_t* out, const tri_mul_params_t* p, void* stream)
         return rc;
     }
 
-    // fp32 copies for the VALU kernels.
     std::vector<float> f_lnw(lnw.begin(), lnw.end()), f_lnb(lnb.begin(), lnb.end());
     std::vector<float> f_low(low.begin(), low.end()), f_lob(lob.begin(), lob.end());
-    std::vector<float> proj4((size_t)cz * c * 4), wo_t((size_t)c * cz), wg_t((size_t)cz * cz);
-    for (int d = 0; d < cz; ++d)
-        for (int ch = 0; ch < c; ++ch) {
-            float* q = &proj4[((size_t)d * c + ch) * 4];
-            q[0] = (float)wa[(size_t)ch * cz + d];
-            q[1] = (float)wga[(size_t)ch * cz + d];
-            q[2] = (float)wb[(size_t)ch * cz + d];
-            q[3] = (float)wgb[(size_t)ch * cz + d];
-        }
-    for (int d = 0; d < cz; ++d)
-        for (int ch = 0; ch < c; ++ch) wo_t[(size_t)ch * cz + d] = (float)wo[(size_t)d * c + ch];
-    for (int d = 0; d < cz; ++d)
-        for (int e2 = 0; e2 < cz; ++e2) wg_t[(size_t)e2 * cz + d] = (float)wg[(size_t)d * cz + e2];
-
     if (!rc) rc = upload(h, &h->w.ln_in_w, f_lnw, s);
     if (!rc) rc = upload(h, &h->w.ln_in_b, f_lnb, s);
     if (!rc) rc = upload(h, &h->w.ln_out_w, f_low, s);
     if (!rc) rc = upload(h, &h->w.ln_out_b, f_lob, s);
-    if (!rc) rc = upload(h, &h->w.proj4, proj4, s);
-    if (!rc) rc = upload(h, &h->w.wo_t, wo_t, s);
-    if (!rc) rc = upload(h, &h->w.wg_t, wg_t, s);
+    if (!rc && p->dtype == TRI_MUL_F32) {
+        // fp32 MFMA operands: 32-row blocks in operand order (DeviceWeights::proj_f)
+        auto block = [](const std::vector<double>& src, int row0, std::vector<float>& dst) {
+            for (int q = 0; q < 16; ++q)
+                for (int l = 0; l < 64; ++l)
+                    for (int e2 = 0; e2 < 4; ++e2)
+                        dst.push_back((float)src[(size_t)(row0 + l % 32) * 128 + 8 * q + 4 * (l / 32) + e2]);
+        };
+        std::vector<float> pf, ef;
+        for (int g = 0; g < 8; ++g) {
+            block(g < 4 ? wa : wb, 32 * (g & 3), pf);
+            block(g < 4 ? wga : wgb, 32 * (g & 3), pf);
+        }
+        for (int g = 0; g < 4; ++g) {
+            block(wo, 32 * g, ef);
+            block(wg, 32 * g, ef);
+        }
+        rc = upload(h, &h->w.proj_f, pf, s);
+        if (!rc) rc = upload(h, &h->w.epi_f, ef, s);
+    }
     if (!rc) {
         std::vector<uint8_t> zeros((size_t)trimul::kMaskStageBytes, 0);
         rc = upload(h, &h->w.kmask_pad, zeros, s);

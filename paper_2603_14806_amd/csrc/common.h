@@ -53,6 +53,11 @@ __device__ __forceinline__ float sum_lanes4(float v) {
     return v;
 }
 
+// Element e (a compile-time constant after unrolling) of a float4.
+__device__ __forceinline__ float f4_get(const float4& v, int e) {
+    return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
+}
+
 template <typename T> struct Store;
 template <> struct Store<float> {
     static __device__ __forceinline__ float ld(const float* p) { return *p; }

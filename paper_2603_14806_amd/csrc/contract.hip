@@ -6,8 +6,8 @@
 //
 // m_k is an optional token mask over k (used by the block path, where the
 // panels arrive unmasked).  The bf16 path runs on gfx950 matrix cores
-// (v_mfma_f32_32x32x16_bf16, fp32 accumulation); the fp32 path is a plain
-// LDS-tiled VALU kernel.
+// (v_mfma_f32_32x32x16_bf16, fp32 accumulation), and so does the fp32 path
+// (v_mfma_f32_32x32x2_f32).
 #include <vector>
 
 #include "common.h"
@@ -433,56 +433,153 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
     }
 }
 
-// ---------------------------------------------------------------- fp32 VALU
+// ---------------------------------------------------------------- fp32 MFMA
+//
+// The fp32 storage path on v_mfma_f32_32x32x2_f32.  One work-group of 4
+// waves (2 x 2) per T x T output tile, steps of 32 k through LDS (rows
+// padded to 36 floats: the 16 rows a 16-byte read serves per cycle start in
+// distinct banks), the next step's global loads in registers while the
+// current one is multiplied.  Lane l takes k = 8 q + 4 (l / 32) + e of its
+// row for element e of the 16-byte read q, on both operands, so one read
+// feeds four products.  Bound by the matrix cores; several work-groups per
+// compute unit cover each other's barriers and loads.  k past K and masked k
+// are zeroed in both operands (either may hold a NaN there).  N = 384: 309 us
+// with scalar FMAs, now 128 (113 TFLOP/s); N = 64: 13 and 7.5.
+constexpr int kFr = 36;   // row stride (floats) of an operand in LDS
 
-template <bool BLOCKED>
-__global__ __launch_bounds__(256) void k2_contract_f32(const float* __restrict__ A, const float* __restrict__ B,
-                                                      float* __restrict__ C, int M, int N, int K, int64_t lda,
-                                                      int64_t ldb, int64_t ldc, int64_t sA, int64_t sB,
-                                                      int64_t sC, int accumulate,
-                                                      const uint8_t* __restrict__ kmask) {
-    __shared__ float As[16][64 + 4], Bs[16][64 + 4];
-    const int64_t ch = blockIdx.z;
-    const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-    const PanelGeom ga = panel_geom(M, K), gb = panel_geom(N, K);
-    auto a_at = [&](int64_t r, int64_t k) { return BLOCKED ? A[panel_off(ga, ch, r, k)] : A[ch * sA + r * lda + k]; };
-    auto b_at = [&](int64_t r, int64_t k) { return BLOCKED ? B[panel_off(gb, ch, r, k)] : B[ch * sB + r * ldb + k]; };
-    float* Cr = C + ch * sC;
-    const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
+template <int T, bool BLOCKED>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2)))
+void k2_contract_f32(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int M, int N, int K,
+                     int64_t lda, int64_t ldb, int64_t ldc, int64_t sA, int64_t sB, int64_t sC, int tm, int tn,
+                     int batch, int accumulate, const uint8_t* __restrict__ kmask) {
+    constexpr int WB = T / 64;    // 32 x 32 blocks per wave and side
+    constexpr int RL = T / 32;    // 16-byte loads per thread, operand and step
+    __shared__ __attribute__((aligned(16))) float As[T * kFr], Bs[T * kFr];
+    // Work-groups go to the XCDs round-robin by index: give each XCD a
+    // contiguous run of tiles, so that a channel's panels stay in one L2.
+    const unsigned nu = gridDim.x, per = nu >> 3, extra = nu & 7, xcd = blockIdx.x & 7;
+    const unsigned u = xcd * per + min(xcd, extra) + (blockIdx.x >> 3);   // a bijection of [0, nu)
+    const int ch = (int)(u / (unsigned)(tm * tn)), rem = (int)(u - (unsigned)ch * (unsigned)(tm * tn));
+    const int m0 = (rem / tn) * T, n0 = (rem % tn) * T;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int rl = lane & 31, hi = lane >> 5;
+    const int wm = (wave >> 1) * (T / 2), wn = (wave & 1) * (T / 2);
+
+    // This thread's loads: rows t / 8 + 32 s of the tile, k = 4 (t % 8) .. + 3
+    // of the step, straight-line range-checked buffer loads that stay in
+    // flight behind the products (rows past a row-major operand read zeros).
+    // What must not reach the sums -- k past K, masked k -- is zeroed when a
+    // step that holds any is staged.
+    const int kk = 4 * (t & 7);
+    auto desc = [&](const float* X, int rows, int64_t ld, int64_t stride, int r0, int live, uint32_t& off, uint32_t& rs, uint32_t& ks) {
+        const PanelGeom g = panel_geom(rows, K);
+        const int64_t base = BLOCKED ? ((int64_t)ch * g.tiles_r + r0 / kBlkRows) * g.ksteps * (kBlkRows * kBlkK)
+                                     : ch * stride + (int64_t)r0 * ld;
+        const uint32_t bytes = BLOCKED ? (uint32_t)g.ksteps * (kBlkRows * kBlkK * 4) : (uint32_t)live * (uint32_t)ld * 4u;
+        rs = BLOCKED ? kBlkK * 4 : (uint32_t)ld * 4u;                    // bytes between rows
+        ks = BLOCKED ? kBlkRows * kBlkK * 4 : kBlkK * 4;                 // bytes between steps
+        off = (uint32_t)((BLOCKED ? r0 % kBlkRows : 0) + (t >> 3)) * rs + 4 * kk;
+        return make_rsrc(X + base, bytes);
+    };
+    uint32_t oa, ob, rsa, rsb, ksa, ksb;
+    const __amdgpu_buffer_rsrc_t ra = desc(A, M, lda, sA, m0, min(T, M - m0), oa, rsa, ksa);
+    const __amdgpu_buffer_rsrc_t rb = desc(B, N, ldb, sB, n0, min(T, N - n0), ob, rsb, ksb);
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kmask, kmask ? (uint32_t)K : 0u);
+    float4 va[RL], vb[RL];
+    uint32_t km[4];
+    auto load = [&](int k0) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int idx = t + 256 * s, row = idx >> 4, kk = idx & 15, k = k0 + kk;
-            const bool kv = k < K && (!kmask || kmask[k] != 0);
-            As[kk][row] = (m0 + row < M && kv) ? a_at(m0 + row, k) : 0.f;
-            Bs[kk][row] = (n0 + row < N && kv) ? b_at(n0 + row, k) : 0.f;
+        for (int s = 0; s < RL; ++s) {
+            va[s] = __builtin_bit_cast(float4, buf_load16(ra, oa + 32u * s * rsa));
+            vb[s] = __builtin_bit_cast(float4, buf_load16(rb, ob + 32u * s * rsb));
+        }
+        oa += ksa;
+        ob += ksb;
+        if (!BLOCKED) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) km[e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rk, k0 + kk + e, 0, 0);
+        }
+    };
+    auto zero_dead = [&](int k0) {
+        uint32_t on[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            on[e] = k0 + kk + e < K && (BLOCKED || !kmask || km[e] != 0) ? 0xffffffffu : 0u;
+        auto clear = [&](float4& v) {
+            const uint4 u = __builtin_bit_cast(uint4, v);
+            v = __builtin_bit_cast(float4, make_uint4(u.x & on[0], u.y & on[1], u.z & on[2], u.w & on[3]));
+        };
+#pragma unroll
+        for (int s = 0; s < RL; ++s) {
+            clear(va[s]);
+            clear(vb[s]);
+        }
+    };
+    f32x16_t acc[WB][WB];
+#pragma unroll
+    for (int i = 0; i < WB; ++i)
+#pragma unroll
+        for (int j = 0; j < WB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    load(0);
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        if (k0 + 32 > K || (!BLOCKED && kmask)) zero_dead(k0);
+        __syncthreads();   // every wave has read the previous step
+#pragma unroll
+        for (int s = 0; s < RL; ++s) {
+            *reinterpret_cast<float4*>(&As[((t >> 3) + 32 * s) * kFr + kk]) = va[s];
+            *reinterpret_cast<float4*>(&Bs[((t >> 3) + 32 * s) * kFr + kk]) = vb[s];
         }
         __syncthreads();
+        load(k0 + 32);   // past the last step: read and never staged (in range of the operand, or zeros)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
+        for (int q = 0; q < 4; ++q) {
+            float4 a[WB], b[WB];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = As[kk][ty * 4 + i];
-                b[i] = Bs[kk][tx * 4 + i];
+            for (int i = 0; i < WB; ++i) {
+                a[i] = *reinterpret_cast<const float4*>(&As[(wm + 32 * i + rl) * kFr + 8 * q + 4 * hi]);
+                b[i] = *reinterpret_cast<const float4*>(&Bs[(wn + 32 * i + rl) * kFr + 8 * q + 4 * hi]);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+                for (int i = 0; i < WB; ++i)
+#pragma unroll
+                    for (int j = 0; j < WB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f4_get(a[i], e), f4_get(b[j], e), acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
     }
+    // lane holds column lane % 32; register r holds row 8 (r / 4) + 4 (lane / 32) + r % 4
     const int64_t jblocks = (N + kResJ - 1) / kResJ;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < WB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-            if (row < M && col < N) {
-                float* p = BLOCKED ? C + result_off(jblocks, (int)gridDim.z, ch, row, col) : Cr + (int64_t)row * ldc + col;
-                *p = accumulate ? *p + acc[i][j] : acc[i][j];
+        for (int j = 0; j < WB; ++j) {
+            const int col = n0 + wn + 32 * j + rl, row0 = m0 + wm + 32 * i + 4 * hi;
+            if (col >= N) continue;
+            float* p = BLOCKED ? C + result_off(jblocks, batch, ch, row0, col) : C + ch * sC + (int64_t)row0 * ldc + col;
+            const int64_t rs = BLOCKED ? jblocks * batch * kResJ : ldc;
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
+            if (accumulate) {   // all 16 loads together; a row past M reads the block's first one
+                if (row0 >= M) continue;
+                float old[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dr = 8 * (r >> 2) + (r & 3);
+                    old[r] = p[(row0 + dr < M ? dr : 0) * rs];
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] += old[r];
+            }
+            const bool full = m0 + T <= M;   // uniform: no per-row guards
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int dr = 8 * (r >> 2) + (r & 3);
+                if (full || row0 + dr < M) p[dr * rs] = v[r];
             }
         }
 }
@@ -646,13 +743,24 @@ hipError_t launch_contract(int dtype, int blocked, const void* A, const void* B,
                            int64_t sB, int64_t sC, int batch, int accumulate, const uint8_t* kmask, int cus,
                            hipStream_t s) {
     if (dtype == 0) {
-        const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((N + 63) / 64), (unsigned)batch);
-        if (blocked)
-            hipLaunchKernelGGL(k2_contract_f32<true>, grid, dim3(256), 0, s, (const float*)A, (const float*)B, C,
-                               (int)M, (int)N, (int)K, lda, ldb, ldc, sA, sB, sC, accumulate, kmask);
-        else
-            hipLaunchKernelGGL(k2_contract_f32<false>, grid, dim3(256), 0, s, (const float*)A, (const float*)B, C,
-                               (int)M, (int)N, (int)K, lda, ldb, ldc, sA, sB, sC, accumulate, kmask);
+        // Tiles of 128 halve the L2 traffic of a product, tiles of 64 give four
+        // times the work-groups and pad less.  128 from 16 tiles per compute
+        // unit on where its padding costs at most 5% (N = 1024: 2.01 against
+        // 2.18 ms; equal at N = 512; at N = 384 148 against 128 us, at N = 700
+        // 792 against 719, at N = 64 8.9 against 7.5).
+        const int64_t t1 = (M + 127) / 128 * ((N + 127) / 128), t2 = (M + 63) / 64 * ((N + 63) / 64);
+        const bool wide = t1 * batch >= 16 * (int64_t)cus && 80 * t1 <= 21 * t2;
+        const int T = wide ? 128 : 64;
+        const int tm = (int)((M + T - 1) / T), tn = (int)((N + T - 1) / T);
+#define K2_F32(T_, BL_)                                                                                             \
+    hipLaunchKernelGGL((k2_contract_f32<T_, BL_>), dim3((unsigned)(tm * tn * batch)), dim3(256), 0, s,              \
+                       (const float*)A, (const float*)B, C, (int)M, (int)N, (int)K, lda, ldb, ldc, sA, sB, sC, tm, \
+                       tn, batch, accumulate, kmask)
+        if (wide && blocked) K2_F32(128, true);
+        else if (wide) K2_F32(128, false);
+        else if (blocked) K2_F32(64, true);
+        else K2_F32(64, false);
+#undef K2_F32
         return hipGetLastError();
     }
     constexpr int BM = 256;

@@ -3,89 +3,144 @@
 // triangle update, Section 3.3).  Reads the channel-major fp32 contraction
 // result and writes the pair-major update [rows][cols][c_z].
 //
-// Work unit: 64 consecutive pairs of one output row.
+// Work unit: 32 consecutive pairs of one output row.
 #include "common.h"
 #include "kernels.h"
 
 namespace trimul {
 namespace {
 
-constexpr int kPairs = 64;
+// ------------------------------------------------------------ fp32 MFMA
+//
+// The fp32 storage path on v_mfma_f32_32x32x2_f32, as the fp32 projection:
+// units of 32 pairs of one row, y = LN_out(C) and x = LN_in(z) in LDS as the
+// A operand, W_o and W_g from L2 in operand order (DeviceWeights::epi_f) as
+// the B operand, wave w owning output channels 32 w .. + 31, so that a
+// register holds 32 consecutive channels of a pair and the stores are
+// 128-byte runs.  Bound by the matrix cores and, next to them, by its memory
+// traffic: 469 us with scalar FMAs at N = 384, 59 us at N = 64; now 94 and 8.
+// Units of 64 pairs (half the weight reads, but two work-groups a compute
+// unit instead of four) took 128 and 16, a persistent form with the next
+// unit's C and z in registers 131 and 11.
+constexpr int kPf = 32;        // pairs per unit
+constexpr int kYf = 128 + 4;   // row stride (floats) of the activations in LDS
 
-template <typename T, typename TO>
-__global__ __launch_bounds__(256) void k3_epilogue_valu(
-    EpilogueArgs a, int64_t nchunk, const float* __restrict__ wo_t, const float* __restrict__ wg_t,
-    const float* __restrict__ lnin_w, const float* __restrict__ lnin_b,
-    const float* __restrict__ lnout_w, const float* __restrict__ lnout_b, float eps) {
-    __shared__ float cs[kPairs][kCh + 1];
-    __shared__ float xs[kPairs][kCz + 1];
-    const int t = threadIdx.x;
-    const int64_t i = blockIdx.x / nchunk;
-    const int64_t j0 = (blockIdx.x % nchunk) * kPairs;
-    const int np = (int)min<int64_t>(kPairs, a.cols - j0);
-    const T* z = static_cast<const T*>(a.z);
+template <typename TO>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(4)))
+void k3_epilogue_f32(EpilogueArgs a, int nchunk, const float4* __restrict__ wf, const float* __restrict__ lnin_w,
+                     const float* __restrict__ lnin_b, const float* __restrict__ lnout_w,
+                     const float* __restrict__ lnout_b, float eps) {
+    __shared__ __attribute__((aligned(16))) float ys[kPf * kYf], xs[kPf * kYf];
+    __shared__ uint32_t mk[kPf];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int rl = lane & 31, hi = lane >> 5;
+    const int lp = t >> 3, lq = t & 7;   // LayerNorms: pair lp, channels 4 (lq + 8 k) .. + 3
+    const int64_t i = blockIdx.x / (unsigned)nchunk;
+    const int64_t j0 = (int64_t)(blockIdx.x % (unsigned)nchunk) * kPf;
+    const int np = (int)min<int64_t>(kPf, a.cols - j0);
+    const float* z = static_cast<const float*>(a.z);
 
-    const int64_t jblocks = (a.cols + kResJ - 1) / kResJ;
-    for (int idx = t; idx < kPairs * kCh; idx += 256) {
-        const int c = idx / kPairs, p = idx % kPairs;
-        cs[p][c] = p < np ? (a.cblocked ? a.C[result_off(jblocks, kCh, c, i, j0 + p)] : a.C[c * a.sc + i * a.ldc + j0 + p])
-                          : 0.f;
+    float4 zv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        zv[k] = lp < np ? *reinterpret_cast<const float4*>(z + (i * a.cols + j0 + lp) * kCz + 4 * (lq + 8 * k))
+                        : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a.cblocked) {   // 32 pairs x 128 channels are one contiguous block, [channel][32]
+        const int64_t jblocks = (a.cols + kResJ - 1) / kResJ;
+        const float4* blk = reinterpret_cast<const float4*>(a.C + result_off(jblocks, kCh, 0, i, j0));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float4 v = blk[t + 256 * s];
+            const int c = (t >> 3) + 32 * s, p = 4 * (t & 7);
+            ys[p * kYf + c] = v.x;
+            ys[(p + 1) * kYf + c] = v.y;
+            ys[(p + 2) * kYf + c] = v.z;
+            ys[(p + 3) * kYf + c] = v.w;
+        }
+    } else {
+        for (int idx = t; idx < kPf * kCh; idx += 256) {
+            const int c = idx / kPf, p = idx % kPf;
+            ys[p * kYf + c] = p < np ? a.C[c * a.sc + i * a.ldc + j0 + p] : 0.f;
+        }
     }
-    for (int idx = t; idx < kPairs * kCz; idx += 256) {
-        const int p = idx / kCz, d = idx % kCz;
-        xs[p][d] = p < np ? Store<T>::ld(z + ((i * a.cols) + j0 + p) * kCz + d) : 0.f;
-    }
+    if (t < kPf)
+        mk[t] = t < np && (!a.mask || (a.mask[a.row0 + i] != 0 && a.mask[a.col0 + j0 + t] != 0)) ? 0xffffffffu : 0u;
+    // LayerNorm of 128 values spread over 8 lanes
+    auto norm = [&](float4 (&v)[4], const float* gw, const float* gb) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += (v[k].x + v[k].y) + (v[k].z + v[k].w);
+        s = sum_lanes8(s);
+        const float mu = s * (1.0f / 128);
+        float q2 = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k].x -= mu; v[k].y -= mu; v[k].z -= mu; v[k].w -= mu;
+            q2 += (v[k].x * v[k].x + v[k].y * v[k].y) + (v[k].z * v[k].z + v[k].w * v[k].w);
+        }
+        q2 = sum_lanes8(q2);
+        const float rs = rsqrtf(q2 * (1.0f / 128) + eps);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4 g = *reinterpret_cast<const float4*>(gw + 4 * (lq + 8 * k));
+            const float4 b = *reinterpret_cast<const float4*>(gb + 4 * (lq + 8 * k));
+            v[k] = make_float4(v[k].x * rs * g.x + b.x, v[k].y * rs * g.y + b.y, v[k].z * rs * g.z + b.z, v[k].w * rs * g.w + b.w);
+        }
+    };
+    norm(zv, lnin_w, lnin_b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(&xs[lp * kYf + 4 * (lq + 8 * k)]) = zv[k];
     __syncthreads();
-
-    {   // both LayerNorms, four lanes per pair
-        const int p = t >> 2, q = t & 3;
-        float s1 = 0.f, s2 = 0.f;
-        for (int d = q * 32; d < q * 32 + 32; ++d) {
-            s1 += cs[p][d];
-            s2 += xs[p][d];
-        }
-        s1 = sum_lanes4(s1);
-        s2 = sum_lanes4(s2);
-        const float mu1 = s1 * (1.0f / kCh), mu2 = s2 * (1.0f / kCz);
-        float v1 = 0.f, v2 = 0.f;
-        for (int d = q * 32; d < q * 32 + 32; ++d) {
-            const float e1 = cs[p][d] - mu1, e2 = xs[p][d] - mu2;
-            v1 += e1 * e1;
-            v2 += e2 * e2;
-        }
-        v1 = sum_lanes4(v1);
-        v2 = sum_lanes4(v2);
-        const float r1 = rsqrtf(v1 * (1.0f / kCh) + eps), r2 = rsqrtf(v2 * (1.0f / kCz) + eps);
-        for (int d = q * 32; d < q * 32 + 32; ++d) {
-            cs[p][d] = (cs[p][d] - mu1) * r1 * lnout_w[d] + lnout_b[d];
-            xs[p][d] = (xs[p][d] - mu2) * r2 * lnin_w[d] + lnin_b[d];
-        }
+    {   // pairs past the row's end hold the layout's padding: their products are dropped
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(&ys[lp * kYf + 4 * (lq + 8 * k)]);
+        norm(v, lnout_w, lnout_b);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(&ys[lp * kYf + 4 * (lq + 8 * k)]) = v[k];
     }
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wf + (int64_t)wave * 2 * 16 * 64, 2 * 16 * 1024);
+    f32x16_t ay, ag;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ay[r] = ag[r] = 0.f;
+    struct Ops { float4 wo, wg, y, x; };
+    auto loadw = [&](int q, Ops& o) {   // [W_o, W_g][k group q][lane]
+        o.wo = __builtin_bit_cast(float4, buf_load16(rw, (uint32_t)(q * 1024 + 16 * lane)));
+        o.wg = __builtin_bit_cast(float4, buf_load16(rw, (uint32_t)((16 + q) * 1024 + 16 * lane)));
+    };
+    auto loada = [&](int q, Ops& o) {
+        o.y = *reinterpret_cast<const float4*>(&ys[rl * kYf + 8 * q + 4 * hi]);
+        o.x = *reinterpret_cast<const float4*>(&xs[rl * kYf + 8 * q + 4 * hi]);
+        __builtin_amdgcn_sched_barrier(0);   // issued here, a group ahead of their products
+    };
+    auto products = [&](const Ops& o) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            ay = __builtin_amdgcn_mfma_f32_32x32x2f32(f4_get(o.y, e), f4_get(o.wo, e), ay, 0, 0, 0);
+            ag = __builtin_amdgcn_mfma_f32_32x32x2f32(f4_get(o.x, e), f4_get(o.wg, e), ag, 0, 0, 0);
+        }
+    };
+    Ops o0, o1;
+    loadw(0, o0);
     __syncthreads();
-
-    const int d = t & (kCz - 1), half = t >> 7;
-    float y[32], gl[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) y[q] = gl[q] = 0.f;
-    for (int c = 0; c < kCh; ++c) {
-        const float w = wo_t[c * kCz + d];
-#pragma unroll
-        for (int q = 0; q < 32; ++q) y[q] += w * cs[half * 32 + q][c];
+    loada(0, o0);
+#pragma unroll 1
+    for (int q = 0; q < 16; q += 2) {
+        loadw(q + 1, o1);
+        loada(q + 1, o1);
+        products(o0);
+        loadw(q < 14 ? q + 2 : 0, o0);   // the last one goes unused
+        loada(q < 14 ? q + 2 : 0, o0);
+        products(o1);
     }
-    for (int e = 0; e < kCz; ++e) {
-        const float w = wg_t[e * kCz + d];
+    // lane holds output channel 32 wave + lane % 32; register r holds pair 8 (r / 4) + 4 (lane / 32) + r % 4
+    TO* out = static_cast<TO*>(a.out) + (i * a.cols + j0) * kCz + 32 * wave + rl;
 #pragma unroll
-        for (int q = 0; q < 32; ++q) gl[q] += w * xs[half * 32 + q][e];
-    }
-    const bool mi = a.mask ? a.mask[a.row0 + i] != 0 : true;
-    TO* out = static_cast<TO*>(a.out);
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-        const int p = half * 32 + q;
-        if (p < np) {
-            const bool m = mi && (a.mask ? a.mask[a.col0 + j0 + p] != 0 : true);
-            Store<TO>::st(out + ((i * a.cols) + j0 + p) * kCz + d, m ? sigmoidf_(gl[q]) * y[q] : 0.f);
-        }
+    for (int r = 0; r < 16; ++r) {
+        const int p = 8 * (r >> 2) + 4 * hi + (r & 3);
+        const float v = __uint_as_float(__float_as_uint(sigmoidf_(ag[r]) * ay[r]) & mk[p]);
+        if (p < np) Store<TO>::st(out + p * kCz, v);
     }
 }
 
@@ -583,11 +638,11 @@ void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z,
     wait_vmcnt_pinned<0>();   // the ring load past the last unit lands before the work-group ends
 }
 
-template <typename T, typename TO>
-hipError_t launch_valu(const DeviceWeights& w, const EpilogueArgs& a, hipStream_t s) {
-    const int64_t nchunk = (a.cols + kPairs - 1) / kPairs;
-    hipLaunchKernelGGL((k3_epilogue_valu<T, TO>), dim3((unsigned)(a.rows * nchunk)), dim3(256), 0, s, a,
-                       nchunk, w.wo_t, w.wg_t, w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
+template <typename TO>
+hipError_t launch_f32(const DeviceWeights& w, const EpilogueArgs& a, hipStream_t s) {
+    const int64_t nchunk = (a.cols + kPf - 1) / kPf;
+    hipLaunchKernelGGL(k3_epilogue_f32<TO>, dim3((unsigned)(a.rows * nchunk)), dim3(256), 0, s, a, (int)nchunk,
+                       reinterpret_cast<const float4*>(w.epi_f), w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
     return hipGetLastError();
 }
 
@@ -619,7 +674,7 @@ hipError_t launch_mfma(const DeviceWeights& w, const EpilogueArgs& a, hipStream_
 hipError_t launch_epilogue(int dtype, int out_dtype, const DeviceWeights& w, const EpilogueArgs& a,
                            hipStream_t s) {
     if (dtype == 0)
-        return out_dtype == 0 ? launch_valu<float, float>(w, a, s) : launch_valu<float, bf16_t>(w, a, s);
+        return out_dtype == 0 ? launch_f32<float>(w, a, s) : launch_f32<bf16_t>(w, a, s);
     return out_dtype == 0 ? launch_mfma<float>(w, a, s) : launch_mfma<bf16_t>(w, a, s);
 }
 

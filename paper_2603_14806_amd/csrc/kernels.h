@@ -10,14 +10,15 @@ namespace trimul {
 
 // Repacked, device-resident layer parameters (owned by the handle).
 struct DeviceWeights {
-    // fp32 copies used by the VALU kernels (both storage types)
+    // fp32 LayerNorm parameters (both storage types)
     float* ln_in_w = nullptr;   // [c_z]
     float* ln_in_b = nullptr;   // [c_z]
     float* ln_out_w = nullptr;  // [c]
     float* ln_out_b = nullptr;  // [c]
-    float* proj4 = nullptr;     // [c_z][c][4]: (W_a, W_ga, W_b, W_gb)[c][d] at [d][c][*]
-    float* wo_t = nullptr;      // [c][c_z]:   W_o[d][c] at [c][d]
-    float* wg_t = nullptr;      // [c_z][c_z]: W_g[d][e] at [e][d]
+    // fp32 MFMA operands (fp32 storage only): blocks of 32 weight rows, [block][16 k groups][64 lanes][4]
+    // with row l % 32 and k = 8 q + 4 (l / 32) + e at lane l, element e of k group q
+    float* proj_f = nullptr;    // 8 gated groups (a's four 32-channel groups, then b's) x (value, gate) blocks
+    float* epi_f = nullptr;     // 4 groups of 32 output channels x (W_o, W_g) blocks
     // bf16 copies used by the MFMA kernels (bf16 storage only)
     uint16_t* proj_bf = nullptr;  // [4*c][c_z]: rows ordered per 32-channel group g:
                                   // W_a[g], W_ga[g], W_b[g], W_gb[g] (32 rows each)

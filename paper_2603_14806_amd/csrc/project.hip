@@ -2,10 +2,10 @@
 // channel-major operands of the contraction (Section 3.3: a, b are gated
 // projections of z; Eq. 2 / Eq. 3 pick which token index is contracted).
 //
-// Work unit: a "line" of 64 pairs that share one output row.  Outgoing line
-// (r, k0): pairs (r, k0..k0+63), A[c][r][k0+p] = a(r, k0+p).  Incoming line
-// (r, k0): pairs (k0..k0+63, r), A[c][r][k0+p] = a(k0+p, r).  Either way the
-// 64 results of one channel are contiguous in A and B.
+// Work unit: a "line" of 32 pairs that share one output row.  Outgoing line
+// (r, k0): pairs (r, k0..k0+31), A[c][r][k0+p] = a(r, k0+p).  Incoming line
+// (r, k0): pairs (k0..k0+31, r), A[c][r][k0+p] = a(k0+p, r).  Either way the 32
+// results of one channel are contiguous in A and B.
 #include <algorithm>
 
 #include "common.h"
@@ -14,77 +14,118 @@
 namespace trimul {
 namespace {
 
-constexpr int kLine = 64;   // pairs per work unit
+// ------------------------------------------------------------ fp32 MFMA
+//
+// The fp32 storage path, on v_mfma_f32_32x32x2_f32 (fp32 operands and sums,
+// 157 TFLOP/s at 2.4 GHz).  A work-group of 4 waves takes a line of 32 pairs
+// and four of the eight gated groups, one per wave: a gated group is 32
+// hidden channels of a or of b, i.e. two 32-row weight blocks (value and
+// gate) whose products land in the same lane and register, so the gating
+// stays in registers.  x goes through LDS (rows padded to 132 floats: the 16
+// rows a 16-byte read serves per cycle start 4 banks apart); the weights
+// stream from L2 as 1 KB loads in operand order (DeviceWeights::proj_f), one
+// k group ahead.  In group q lane l holds k = 8 q + 4 (l / 32) + e of its row
+// in element e, so one 16-byte read feeds four products.  A pair's 128-byte
+// channel runs go straight from the accumulators to the panels.
+//
+// Bound by the matrix cores (4 x 128 x 128 multiply-adds a pair); the scalar
+// kernel it replaces took 595 us at N = 384 and 72 us at N = 64, this one 175
+// and 8 (113 TFLOP/s).  Lines of 64 pairs and all eight groups per
+// work-group (an eighth of the weight reads) gained 2% at N = 512 and took
+// 20 us at N = 64.
+constexpr int kXf = kCz + 4;   // row stride (floats) of x in LDS
+constexpr int kPf = 32;        // pairs per line
 
-// Scalar (VALU) fp32 version; it serves the fp32 storage path.
-template <typename T, bool INCOMING>
-__global__ __launch_bounds__(256) void k1_project_valu(
-    const T* __restrict__ z, const uint8_t* __restrict__ mask, int64_t N, int64_t nchunk,
-    const float4* __restrict__ proj4, const float* __restrict__ lnw, const float* __restrict__ lnb,
-    float eps, T* __restrict__ A, T* __restrict__ B) {
-    __shared__ float xs[kLine][kCz + 1];
-    const int t = threadIdx.x;
-    const int64_t r = blockIdx.x / nchunk;
-    const int64_t k0 = (blockIdx.x % nchunk) * kLine;
-    const int np = (int)min<int64_t>(kLine, N - k0);
+template <bool INCOMING>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(4)))
+void k1_project_f32(const float* __restrict__ z, const uint8_t* __restrict__ mask, int N, const float4* __restrict__ wf,
+                    const float* __restrict__ lnw, const float* __restrict__ lnb, float eps, float* __restrict__ A,
+                    float* __restrict__ B) {
+    __shared__ __attribute__((aligned(16))) float xs[kPf * kXf];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // rows fastest: neighbouring work-groups write neighbouring rows of the
+    // same panel blocks (and read neighbouring pairs when incoming)
+    const int kc = (int)(blockIdx.x / (unsigned)N), r = (int)(blockIdx.x - (unsigned)kc * (unsigned)N);
+    const int k0 = kc * kPf, np = min(kPf, N - k0);
+    const int gg = (int)blockIdx.y * 4 + wave;           // gated group: a's four, then b's
 
-    for (int idx = t; idx < kLine * kCz; idx += 256) {
-        const int p = idx / kCz, d = idx % kCz;
-        float v = 0.f;
-        if (p < np) {
-            const int64_t pair = INCOMING ? (k0 + p) * N + r : r * N + k0 + p;
-            v = Store<T>::ld(z + pair * kCz + d);
-        }
-        xs[p][d] = v;
-    }
-    __syncthreads();
-
-    {   // LayerNorm over c_z, four lanes per pair
-        const int p = t >> 2, q = t & 3;
+    {   // LayerNorm of pair p, 8 lanes each
+        const int p = t >> 3, q = t & 7;
+        const int64_t pair = INCOMING ? (int64_t)(k0 + p) * N + r : (int64_t)r * N + k0 + p;
+        float4 v[4];
         float s = 0.f;
-        for (int d = q * 32; d < q * 32 + 32; ++d) s += xs[p][d];
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        const float mu = s * (1.0f / kCz);
-        float v = 0.f;
-        for (int d = q * 32; d < q * 32 + 32; ++d) {
-            const float e = xs[p][d] - mu;
-            v += e * e;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = p < np ? *reinterpret_cast<const float4*>(z + pair * kCz + 4 * (q + 8 * i))
+                          : make_float4(0.f, 0.f, 0.f, 0.f);
+            s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
         }
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        const float rs = rsqrtf(v * (1.0f / kCz) + eps);
-        for (int d = q * 32; d < q * 32 + 32; ++d) xs[p][d] = (xs[p][d] - mu) * rs * lnw[d] + lnb[d];
+        s = sum_lanes8(s);
+        const float mu = s * (1.0f / kCz);
+        float q2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i].x -= mu; v[i].y -= mu; v[i].z -= mu; v[i].w -= mu;
+            q2 += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+        }
+        q2 = sum_lanes8(q2);
+        const float rs = rsqrtf(q2 * (1.0f / kCz) + eps);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = 4 * (q + 8 * i);
+            const float4 g = *reinterpret_cast<const float4*>(lnw + c), b = *reinterpret_cast<const float4*>(lnb + c);
+            *reinterpret_cast<float4*>(&xs[p * kXf + c]) = make_float4(v[i].x * rs * g.x + b.x, v[i].y * rs * g.y + b.y,
+                                                                       v[i].z * rs * g.z + b.z, v[i].w * rs * g.w + b.w);
+        }
     }
+    const int rl = lane & 31, hi = lane >> 5;
+    const PanelGeom pg = panel_geom(N, N);
+    const int64_t chs = panel_elems(pg);
+    const uint32_t keep = rl < np && (!mask || (mask[r] != 0 && mask[k0 + rl] != 0)) ? 0xffffffffu : 0u;
     __syncthreads();
 
-    const int c = t & (kCh - 1), half = t >> 7;
-    float acc[32][4];
+    // [value, gate][k group q][lane]
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(wf + (int64_t)gg * 2 * 16 * 64, 2 * 16 * 1024);
+    f32x16_t acc[2];
 #pragma unroll
-    for (int q = 0; q < 32; ++q) acc[q][0] = acc[q][1] = acc[q][2] = acc[q][3] = 0.f;
-    for (int d = 0; d < kCz; ++d) {
-        const float4 w = proj4[d * kCh + c];
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int q = 0; q < 32; ++q) {
-            const float x = xs[half * 32 + q][d];
-            acc[q][0] += w.x * x;
-            acc[q][1] += w.y * x;
-            acc[q][2] += w.z * x;
-            acc[q][3] += w.w * x;
-        }
+        for (int i = 0; i < 16; ++i) acc[m][i] = 0.f;
+    struct Ops { float4 w[2], x; };
+    auto load = [&](int q, Ops& o) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+            o.w[m] = __builtin_bit_cast(float4, buf_load16(rw, (uint32_t)((m * 16 + q) * 1024 + 16 * lane)));
+        o.x = *reinterpret_cast<const float4*>(&xs[rl * kXf + 8 * q + 4 * hi]);
+        __builtin_amdgcn_sched_barrier(0);   // issued here, a group ahead of their products
+    };
+    auto products = [&](const Ops& o) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(f4_get(o.w[m], e), f4_get(o.x, e), acc[m], 0, 0, 0);
+    };
+    Ops o0, o1;
+    load(0, o0);
+#pragma unroll 1
+    for (int q = 0; q < 16; q += 2) {
+        load(q + 1, o1);
+        products(o0);
+        load(q < 14 ? q + 2 : 0, o0);   // the last one goes unused
+        products(o1);
     }
-    const bool mr = mask ? mask[r] != 0 : true;
+    // Lane holds pair lane % 32; register i holds channel 8 (i / 4) +
+    // 4 (lane / 32) + i % 4 of the group.
+    float* X = ((gg >> 2) ? B : A) + (32 * (gg & 3) + 4 * hi) * chs + panel_off(pg, 0, r, k0) + rl;
+    float v[16];
 #pragma unroll
-    for (int q = 0; q < 32; ++q) {
-        const int p = half * 32 + q;
-        if (p < np) {
-            const bool m = mr && (mask ? mask[k0 + p] != 0 : true);
-            const float a = m ? sigmoidf_(acc[q][1]) * acc[q][0] : 0.f;
-            const float b = m ? sigmoidf_(acc[q][3]) * acc[q][2] : 0.f;
-            const int64_t off = panel_off(panel_geom(N, N), c, r, k0 + p);
-            Store<T>::st(A + off, a);
-            Store<T>::st(B + off, b);
-        }
+    for (int i = 0; i < 16; ++i)   // a masked pair's are 0, whatever z holds
+        v[i] = __uint_as_float(__float_as_uint(sigmoidf_(acc[1][i]) * acc[0][i]) & keep);
+    if (rl < np) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) X[(8 * (i >> 2) + (i & 3)) * chs] = v[i];
     }
 }
 
@@ -331,22 +372,20 @@ hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ld
 
 hipError_t launch_project(int dtype, const DeviceWeights& w, const void* z, const uint8_t* mask,
                           int64_t N, int incoming, void* A, void* B, hipStream_t s) {
-    const int64_t nchunk = (N + kLine - 1) / kLine;
-    const dim3 grid((unsigned)(N * nchunk)), block(256);
-    const float4* p4 = reinterpret_cast<const float4*>(w.proj4);
     if (dtype == 0) {
+        const dim3 grid((unsigned)(N * ((N + kPf - 1) / kPf)), 2);
+        const float4* wf = reinterpret_cast<const float4*>(w.proj_f);
         if (incoming)
-            hipLaunchKernelGGL((k1_project_valu<float, true>), grid, block, 0, s, (const float*)z, mask, N,
-                               nchunk, p4, w.ln_in_w, w.ln_in_b, w.eps, (float*)A, (float*)B);
+            hipLaunchKernelGGL(k1_project_f32<true>, grid, dim3(256), 0, s, (const float*)z, mask, (int)N, wf,
+                               w.ln_in_w, w.ln_in_b, w.eps, (float*)A, (float*)B);
         else
-            hipLaunchKernelGGL((k1_project_valu<float, false>), grid, block, 0, s, (const float*)z, mask, N,
-                               nchunk, p4, w.ln_in_w, w.ln_in_b, w.eps, (float*)A, (float*)B);
-    } else {
-        hipError_t e = launch_stage_kmask(mask, N, w.kmask_pad, s);
-        if (e != hipSuccess) return e;
-        return launch_project_mfma(w, z, N, w.kmask_pad, 0, N, N, incoming, A, B, s);
+            hipLaunchKernelGGL(k1_project_f32<false>, grid, dim3(256), 0, s, (const float*)z, mask, (int)N, wf,
+                               w.ln_in_w, w.ln_in_b, w.eps, (float*)A, (float*)B);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    hipError_t e = launch_stage_kmask(mask, N, w.kmask_pad, s);
+    if (e != hipSuccess) return e;
+    return launch_project_mfma(w, z, N, w.kmask_pad, 0, N, N, incoming, A, B, s);
 }
 
 }  // namespace trimul
