@@ -219,29 +219,27 @@ int scratch_for(int device, void** ptr) {
 
 // Workspace of the layer backward (bf16 path), in this order: A, B and the
 // four operands of the contraction backward (panels), C, dA, dB (result
-// layout), dx_g [N*N][c_z] fp32, nine unit-block tensors, and the partial
+// layout), dx_g [N*N][c_z] fp32, five unit-block tensors, and the partial
 // sums of the weight-gradient reductions.
 struct BwdLayout {
     size_t panel, result, dxg, block, part_eb, part_pb, part_w, part_w4, total;
     int grid_pair;   // per-pair stages: one 512-thread work-group per compute unit
-    int grid_w;      // weight-gradient sums: two 256-thread work-groups per compute unit
     int grid_w4;     // the four sums over the x blocks: one 512-thread work-group per compute unit
 };
 BwdLayout bwd_layout(tri_mul_handle_t h, int64_t N) {
     BwdLayout L;
     const int64_t units = N * ((N + 31) / 32);
     L.grid_pair = trimul::backward_grid(units, h->w.cus, 1);
-    L.grid_w = trimul::backward_grid(units, h->w.cus, 2);
     L.panel = round256(panel_bytes(N, h->c, h->dtype));
     L.result = round256(result_bytes(N, h->c));
     L.dxg = round256((size_t)N * (size_t)N * (size_t)h->c_z * 4);
     L.block = round256((size_t)units * 128 * 32 * 2);
     L.part_eb = round256((size_t)L.grid_pair * 2 * 128 * 4);
     L.part_pb = round256((size_t)L.grid_pair * 2 * 128 * 4);
-    L.part_w = round256((size_t)L.grid_w * 128 * 128 * 4);
+    L.part_w = round256((size_t)2 * L.grid_pair * 128 * 128 * 4);
     L.grid_w4 = trimul::backward_grid(units, h->w.cus, 1);
     L.part_w4 = round256((size_t)4 * L.grid_w4 * 128 * 128 * 4);
-    L.total = 3 * L.panel + 3 * L.result + L.dxg + 9 * L.block + L.part_eb + L.part_pb + L.part_w + L.part_w4;
+    L.total = 3 * L.panel + 3 * L.result + L.dxg + 5 * L.block + L.part_eb + L.part_pb + L.part_w + L.part_w4;
     return L;
 }
 
@@ -278,20 +276,20 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
     float* dxg = reinterpret_cast<float*>(take(L.dxg));
     trimul::BackwardBlocks bb;
     using trimul::bf16_t;
-    bf16_t** blk[] = {&bb.du, &bb.y, &bb.dgg, &bb.xe, &bb.dpa, &bb.dga, &bb.dpb, &bb.dgb, &bb.xp};
+    bf16_t** blk[] = {&bb.dpa, &bb.dga, &bb.dpb, &bb.dgb, &bb.xp};
     for (bf16_t** q : blk) *q = reinterpret_cast<bf16_t*>(take(L.block));
     float* peb = reinterpret_cast<float*>(take(L.part_eb));
     float* ppb = reinterpret_cast<float*>(take(L.part_pb));
     float* pw = reinterpret_cast<float*>(take(L.part_w));
     float* pw4 = reinterpret_cast<float*>(take(L.part_w4));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int cus = h->w.cus, G = L.grid_pair, GW = L.grid_w, GW4 = L.grid_w4;
+    const int cus = h->w.cus, G = L.grid_pair, GW4 = L.grid_w4;
 
     hipError_t e = hipSuccess;
     if (!saved)   // recompute the forward's operands (stored transposed) and contraction
         e = forward_operands_and_contraction(h, z, mask, N, incoming, const_cast<void*>(A), const_cast<void*>(B),
                                              const_cast<float*>(C), s);
-    if (e == hipSuccess) e = trimul::launch_epilogue_backward(h->out_dtype, h->w, C, z, mask, dout, N, dCp, dxg, bb, peb, G, s);
+    if (e == hipSuccess) e = trimul::launch_epilogue_backward(h->out_dtype, h->w, C, z, mask, dout, N, dCp, dxg, pw, peb, G, s);
     // A and B hold A^T and B^T: dA = dC B is the plain product of the dC panel
     // with the B^T panel, dB = dC^T A reads dC transposed and A^T as it is
     if (e == hipSuccess)
@@ -299,16 +297,13 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
     if (e == hipSuccess) e = trimul::launch_contract_transposed(1, 0, dCp, A, dB, N, N, N, h->c, cus, s);
     if (e == hipSuccess) e = trimul::launch_projection_backward(h->w, z, mask, N, incoming, dA, dB, dxg, dz, bb, ppb, G, s);
     constexpr int kW = 128 * 128;
-    if (e == hipSuccess) e = trimul::launch_wgrad(bb.du, bb.y, N, pw, GW, s);
-    const trimul::SumTask sum_wo{pw, g->w_o, GW, kW, kW, 0};
-    if (e == hipSuccess) e = trimul::launch_sum_parts(&sum_wo, 1, s);
-    if (e == hipSuccess) e = trimul::launch_wgrad(bb.dgg, bb.xe, N, pw, GW, s);
     // the four projection weights share the x blocks: one pass over them
     const bf16_t* const u4[4] = {bb.dpa, bb.dga, bb.dpb, bb.dgb};
     if (e == hipSuccess) e = trimul::launch_wgrad4(u4, bb.xp, N, pw4, GW4, s);
     const size_t p4 = (size_t)GW4 * kW;
     const trimul::SumTask sums[] = {
-        {pw, g->w_g, GW, kW, kW, 0},
+        {pw, g->w_o, G, kW, kW, 0},
+        {pw + (size_t)G * kW, g->w_g, G, kW, kW, 0},
         {pw4, g->w_a, GW4, kW, kW, 0},
         {pw4 + p4, g->w_ga, GW4, kW, kW, 0},
         {pw4 + 2 * p4, g->w_b, GW4, kW, kW, 0},
@@ -318,7 +313,7 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
         {ppb, g->ln_in_w, G, 256, 128, 0},
         {ppb + 128, g->ln_in_b, G, 256, 128, 0},
     };
-    if (e == hipSuccess) e = trimul::launch_sum_parts(sums, 9, s);
+    if (e == hipSuccess) e = trimul::launch_sum_parts(sums, 10, s);
     if (e != hipSuccess) return hip_fail(e, "backward kernel launch");
     return ok();
 }

@@ -130,10 +130,11 @@ __global__ __launch_bounds__(256) void k_panel_transpose(const T* __restrict__ X
 // ---------------------------------------------------------------- layer backward
 //
 // Work unit = 32 pairs (one row r, columns k = 32 kb .. 32 kb + 31), the
-// unit of the result layout.  Per-pair intermediates that feed the weight
-// gradients are written as "unit blocks": for unit u = r * J + kb, a bf16
-// block [128 channels][32 slots] at u * 4096 elements.  Each weight gradient
-// is then a sum over units of U_block * V_block^T (k_wgrad); slots of pairs
+// unit of the result layout.  The per-pair intermediates that feed the
+// gradients of the projection weights are written as "unit blocks": for unit
+// u = r * J + kb, a bf16 block [128 channels][32 slots] at u * 4096 elements.
+// Each of those gradients is then a sum over units of U_block * V_block^T
+// (k_wgrad4; the epilogue's two weights are summed in place); slots of pairs
 // past N or masked out carry a zero in at least one of the two blocks.
 //
 // The per-pair stages are 128-wide products per unit, run on matrix cores
@@ -152,10 +153,30 @@ constexpr int kPq = 148;      // row stride (floats) of [pair][channel] tiles (t
                               // over their four access patterns)
 constexpr int kArow = 256;    // bytes of one bf16 activation row [128]
 
-// Byte offset of 16-byte chunk ch of row p in a bf16 [q][128] tile; chunks
-// are XOR-swizzled over 16 rows so that the A-operand reads (16 rows, one
-// chunk each) hit distinct banks.
-__device__ __forceinline__ uint32_t arow(int p, int ch) { return (uint32_t)(p * kArow + ((ch ^ (p & 15)) << 4)); }
+// Byte offset of 16-byte chunk ch of row p in a bf16 [q][128] tile.  Chunks
+// are XOR-swizzled by a bijection of the row's low four bits, so the A-operand
+// reads (16 rows, one chunk each) hit distinct banks; row bits 0 and 1 move
+// chunk bits 2 and 3, so the transposing reads (4 consecutive rows, 4
+// consecutive chunks) do too, and row bits 2 and 3 move chunk bits 1 and 2,
+// so the 2-byte stores of 16 columns in rows 4 apart do as well.
+__device__ __forceinline__ uint32_t arow(int p, int ch) {
+    return (uint32_t)(p * kArow + ((ch ^ ((p & 3) << 2) ^ ((p >> 1) & 2) ^ (((p >> 3) & 1) * 5)) << 4));
+}
+
+// A weight-gradient operand from such a tile, transposed: lane l gets column
+// 32 blk + l % 32 of rows 16 ks + 8 (l / 32) .. + 7, i.e. eight pairs of one
+// channel, through two ds_read_b64_tr_b16 (rows + 0 .. 3, then + 4 .. 7; row
+// bit 2 moves chunk bit 1).  Lane 16 g + 4 i + a addresses row 8 (g >> 1) + i
+// and columns 16 (g & 1) + 4 a .. + 3.
+typedef short v4i16_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8_t ld_frag_tr(const char* tile, int lane, int ks, int blk) {
+    typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
+    const int g = lane >> 4, a = lane & 3, q = 16 * ks + 8 * (g >> 1) + ((lane >> 2) & 3);
+    const uint32_t o = arow(q, 4 * blk + 2 * (g & 1) + (a >> 1)) + 8 * (a & 1);
+    const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(tile + o));
+    const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(tile + ((o + 4 * kArow) ^ 32)));
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 // The value itself, hidden from the optimiser: lane indices passed through
 // this inside a loop make the LDS addresses derived from them loop-variant,
@@ -204,19 +225,6 @@ __device__ __forceinline__ void bst_u4(__amdgpu_buffer_rsrc_t r, uint32_t off, u
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, 0);
 }
 
-// 8 bf16 of column `col` of a swizzled row tile, rows q0 .. q0 + 7, packed.
-__device__ __forceinline__ uint4 gather_col8(const char* tile, int q0, int col) {
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int q = q0 + 2 * i;
-        const uint32_t a = *reinterpret_cast<const bf16_t*>(tile + arow(q, col >> 3) + 2 * (col & 7));
-        const uint32_t b = *reinterpret_cast<const bf16_t*>(tile + arow(q + 1, col >> 3) + 2 * (col & 7));
-        w[i] = a | (b << 16);
-    }
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
 // Four bf16 (rows 4 kq .. + 3 of one 16 x 16 result tile) as one 8-byte word.
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
     return make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
@@ -230,17 +238,23 @@ template <> struct DoutRegs<bf16_t> { uint4 a; };
 // y = LN_out(C), u = W_o y, g = sigmoid(W_g x); then
 //   du = dout m g,  dgg = dout m u g (1 - g),  dy = du W_o,  dx_g = dgg W_g,
 //   dC = LN_out backward of dy.
-// Writes dC into the panel (row r, columns k), dx_g [pair][c_z] fp32, unit
-// blocks du, y, dgg, x, and per-work-group sums of dgamma_out, dbeta_out at
-// partial[(2 wg + {0, 1}) * 128 + c].
+// Writes dC into the panel (row r, columns k), dx_g [pair][c_z] fp32, and
+// per-work-group sums of dgamma_out, dbeta_out at partial[(2 wg + {0, 1}) * 128
+// + c] and of the weight gradients
+//   dW_o = sum du y^T,  dW_g = sum dgg x^T   (operands rounded to bf16)
+// at wpart[wg] and wpart[grid + wg], [128][128] each.  Those sums run here,
+// from the activation tiles in LDS (transposing reads) into 64 accumulator
+// registers per lane: the four unit blocks they used to travel in were a third
+// of the kernel's memory traffic, and two passes of their own read them back.
+// N = 1024: 717 us and 2 x 120 us for those passes before, 767 now (about half
+// of it LDS traffic: every wave reads all of the activations).
 template <typename TO>
 __global__ __launch_bounds__(kBT) void k_epilogue_backward(
     const float* __restrict__ C, const bf16_t* __restrict__ z, const uint8_t* __restrict__ mask,
     const TO* __restrict__ dout, int N, int64_t units, const bf16_t* __restrict__ wfwd,
     const bf16_t* __restrict__ wbwd, const float* __restrict__ lniw, const float* __restrict__ lnib,
     const float* __restrict__ lnow, const float* __restrict__ lnob, float eps, bf16_t* __restrict__ dCp,
-    float* __restrict__ dxg, bf16_t* __restrict__ b_du, bf16_t* __restrict__ b_y, bf16_t* __restrict__ b_dgg,
-    bf16_t* __restrict__ b_x, float* __restrict__ partial) {
+    float* __restrict__ dxg, float* __restrict__ wpart, float* __restrict__ partial) {
     __shared__ __align__(16) float cs[kCh * kCs];        // C [c][q]
     __shared__ __align__(16) float dq[kQ * kPq];         // dout [q][d], then dy [q][c]
     __shared__ __align__(16) float dct[kCh * kCs];       // dC [c][q]
@@ -294,6 +308,11 @@ __global__ __launch_bounds__(kBT) void k_epilogue_backward(
     float accg[8], accb[8];                              // dgamma_out, dbeta_out of c = lq + 16 i
 #pragma unroll
     for (int i = 0; i < 8; ++i) accg[i] = accb[i] = 0.f;
+    f32x16_t gwo[2], gwg[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gwo[j][i] = gwg[j][i] = 0.f;
     Pre cur;
     load(blockIdx.x, cur);
     bf16x8_t wo[4], wg[4], wot[4], wgt[4];               // B operands: W_o, W_g rows n; W_o^T, W_g^T rows n
@@ -411,27 +430,18 @@ __global__ __launch_bounds__(kBT) void k_epilogue_backward(
                     au[mb] = mfma16(ld_frag(act[1], o), wo[ks], au[mb]);
                     ag[mb] = mfma16(ld_frag(act[3], o), wg[ks], ag[mb]);
                 }
-            // unit blocks of y and x (bf16 = the hi rows), channel-major
-            *reinterpret_cast<uint4*>(b_y + u * (kCh * kQ) + sc * kQ + 8 * sq) = gather_col8(act[0], 8 * sq, sc);
-            *reinterpret_cast<uint4*>(b_x + u * (kCh * kQ) + sc * kQ + 8 * sq) = gather_col8(act[2], 8 * sq, sc);
             const int d = 16 * w + col;
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) {
-                float vu[4], vg[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int q = 16 * mb + 4 * kq + i;
                     const float o = dq[q * kPq + d] * mq[q];
                     const float g = sigmoidf_(ag[mb][i]);
-                    vu[i] = o * g;
-                    vg[i] = o * au[mb][i] * g * (1.f - g);
                     const uint32_t off = arow(q, d >> 3) + 2 * (d & 7);
-                    st_hilo(act2[0], act2[1], off, vu[i]);
-                    st_hilo(act2[2], act2[3], off, vg[i]);
+                    st_hilo(act2[0], act2[1], off, o * g);
+                    st_hilo(act2[2], act2[3], off, o * au[mb][i] * g * (1.f - g));
                 }
-                const int64_t bo = u * (kCh * kQ) + d * kQ + 16 * mb + 4 * kq;
-                *reinterpret_cast<uint2*>(b_du + bo) = pack4(vu[0], vu[1], vu[2], vu[3]);
-                *reinterpret_cast<uint2*>(b_dgg + bo) = pack4(vg[0], vg[1], vg[2], vg[3]);
             }
         }
         __syncthreads();
@@ -459,6 +469,17 @@ __global__ __launch_bounds__(kBT) void k_epilogue_backward(
                     dq[q * kPq + n] = ay[mb][i];
                     bst_f32(rx, (q * kCz + n) * 4, ax[mb][i]);
                 }
+            // dW_o, dW_g: rows d = 32 (w / 2) .., columns 64 (w % 2) ..
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const int lo = opaque(lane);
+                const bf16x8_t fu = ld_frag_tr(act2[0], lo, ks, w >> 1), fg = ld_frag_tr(act2[2], lo, ks, w >> 1);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    gwo[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fu, ld_frag_tr(act[0], lo, ks, 2 * (w & 1) + j), gwo[j], 0, 0, 0);
+                    gwg[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg, ld_frag_tr(act[2], lo, ks, 2 * (w & 1) + j), gwg[j], 0, 0, 0);
+                }
+            }
         }
         __syncthreads();
         {   // LN_out backward of pair lp: dC = rs (dy gamma - mean(dy gamma) - yh mean(dy gamma yh))
@@ -488,6 +509,17 @@ __global__ __launch_bounds__(kBT) void k_epilogue_backward(
             *reinterpret_cast<uint4*>(dCp + panel_off(pg, sc, r, k0 + 8 * sq)) =
                 make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y), pack_bf16x2(b.z, b.w));
         }
+    }
+    {   // lane holds column lane % 32; register i holds row 8 (i / 4) + 4 (lane / 32) + i % 4
+        float* pw = wpart + (int64_t)blockIdx.x * (kCh * kCh) + (32 * (w >> 1) + 4 * (lane >> 5)) * kCh + 64 * (w & 1) + (lane & 31);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int o = (8 * (i >> 2) + (i & 3)) * kCh + 32 * j;
+                pw[o] = gwo[j][i];
+                pw[(int64_t)gridDim.x * (kCh * kCh) + o] = gwg[j][i];
+            }
     }
     // per-work-group sums over the pairs lanes (lp) through LDS
     __syncthreads();
@@ -805,44 +837,10 @@ void k_projection_backward(
     }
 }
 
-// Weight-gradient sum: W[m][n] = sum over units of U_blk[m][.] . V_blk[n][.]
-// (both [128][32] bf16 unit blocks, the dot product over the 32 slots), on
-// matrix cores: wave w owns rows 32 w .. 32 w + 31 and all 128 columns
-// (4 blocks of v_mfma_f32_32x32x16_bf16, two k-steps per unit).  Each
-// work-group writes one 128 x 128 fp32 partial.
-__global__ __launch_bounds__(256) void k_wgrad(const bf16_t* __restrict__ U, const bf16_t* __restrict__ V,
-                                                int64_t units, float* __restrict__ partial) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int rl = lane & 31, hi = lane >> 5;
-    f32x16_t acc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const bf16_t* ub = U + u * (kCh * kQ);
-        const bf16_t* vb = V + u * (kCh * kQ);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(ub + (32 * w + rl) * kQ + 16 * ks + 8 * hi);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(vb + (32 * j + rl) * kQ + 16 * ks + 8 * hi);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
-            }
-        }
-    }
-    // lane holds column 32 j + rl; register r holds row 32 w + 8 (r / 4) + 4 hi + r % 4
-    float* pw = partial + (int64_t)blockIdx.x * (kCh * kCh);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) pw[(32 * w + 8 * (r >> 2) + 4 * hi + (r & 3)) * kCh + 32 * j + rl] = acc[j][r];
-}
-
 // Four weight gradients that share their second operand (W_a, W_ga, W_b,
-// W_gb all multiply the x blocks): sum over units of U_o V^T for o = 0..3,
-// reading each unit's V block once instead of four times.  8 waves: wave w
+// W_gb all multiply the x blocks): W_o[m][n] = sum over units of U_blk[m][.] .
+// V_blk[n][.] (both [128][32] bf16 unit blocks, the dot product over the 32
+// slots) for o = 0..3, reading each unit's V block once.  8 waves: wave w
 // owns rows 32 (w % 4) .. + 31 of outputs 2 (w / 4) and 2 (w / 4) + 1
 // (two 32 x 128 accumulators); the next unit's operands are loaded while
 // the current one is multiplied.  Partials: [o][grid][128][128].
@@ -975,16 +973,16 @@ int backward_grid(int64_t units, int cus, int per_cu) {
 
 hipError_t launch_epilogue_backward(int out_dtype, const DeviceWeights& w, const float* C, const void* z,
                                     const uint8_t* mask, const void* dout, int64_t N, void* dCp, float* dxg,
-                                    const BackwardBlocks& bb, float* partial, int grid, hipStream_t s) {
+                                    float* wpart, float* partial, int grid, hipStream_t s) {
     const int64_t units = N * ((N + 31) / 32);
     if (out_dtype == 0)
         hipLaunchKernelGGL(k_epilogue_backward<float>, dim3(grid), dim3(kBT), 0, s, C, (const bf16_t*)z, mask,
                            (const float*)dout, (int)N, units, w.epi_bf, w.epit_bf, w.ln_in_w, w.ln_in_b, w.ln_out_w,
-                           w.ln_out_b, w.eps, (bf16_t*)dCp, dxg, bb.du, bb.y, bb.dgg, bb.xe, partial);
+                           w.ln_out_b, w.eps, (bf16_t*)dCp, dxg, wpart, partial);
     else
         hipLaunchKernelGGL(k_epilogue_backward<bf16_t>, dim3(grid), dim3(kBT), 0, s, C, (const bf16_t*)z, mask,
                            (const bf16_t*)dout, (int)N, units, w.epi_bf, w.epit_bf, w.ln_in_w, w.ln_in_b,
-                           w.ln_out_w, w.ln_out_b, w.eps, (bf16_t*)dCp, dxg, bb.du, bb.y, bb.dgg, bb.xe, partial);
+                           w.ln_out_w, w.ln_out_b, w.eps, (bf16_t*)dCp, dxg, wpart, partial);
     return hipGetLastError();
 }
 
@@ -1000,12 +998,6 @@ hipError_t launch_projection_backward(const DeviceWeights& w, const void* z, con
         hipLaunchKernelGGL(k_projection_backward<false>, dim3(grid), dim3(kPT), 0, s, (const bf16_t*)z, mask, (int)N,
                            units, dA, dB, dxg, w.proj_bf, w.projt_bf, w.ln_in_w, w.ln_in_b, w.eps, (bf16_t*)dz,
                            bb.dpa, bb.dga, bb.dpb, bb.dgb, bb.xp, partial);
-    return hipGetLastError();
-}
-
-hipError_t launch_wgrad(const bf16_t* U, const bf16_t* V, int64_t N, float* partial, int grid, hipStream_t s) {
-    const int64_t units = N * ((N + 31) / 32);
-    hipLaunchKernelGGL(k_wgrad, dim3(grid), dim3(256), 0, s, U, V, units, partial);
     return hipGetLastError();
 }
 

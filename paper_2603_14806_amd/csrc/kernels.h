@@ -137,18 +137,16 @@ hipError_t launch_panel_transpose(int dtype, const void* X, void* Y, int64_t N, 
 // Layer backward (bf16 storage).  Unit blocks: per unit of 32 pairs a bf16
 // [128][32] block of one per-pair quantity (see backward.hip).
 struct BackwardBlocks {
-    bf16_t *du, *y, *dgg, *xe;         // from the epilogue backward
-    bf16_t *dpa, *dga, *dpb, *dgb, *xp; // from the projection backward
+    bf16_t *dpa, *dga, *dpb, *dgb, *xp;   // from the projection backward
 };
 // Persistent grid: min(units, per_cu * compute units).
 int backward_grid(int64_t units, int cus, int per_cu);
 hipError_t launch_epilogue_backward(int out_dtype, const DeviceWeights& w, const float* C, const void* z,
                                     const uint8_t* mask, const void* dout, int64_t N, void* dCp, float* dxg,
-                                    const BackwardBlocks& bb, float* partial, int grid, hipStream_t s);
+                                    float* wpart, float* partial, int grid, hipStream_t s);
 hipError_t launch_projection_backward(const DeviceWeights& w, const void* z, const uint8_t* mask, int64_t N,
                                       int incoming, const float* dA, const float* dB, const float* dxg, void* dz,
                                       const BackwardBlocks& bb, float* partial, int grid, hipStream_t s);
-hipError_t launch_wgrad(const bf16_t* U, const bf16_t* V, int64_t N, float* partial, int grid, hipStream_t s);
 // Four weight gradients sharing V: partial[o][grid][128][128] for U[o] V^T, o = 0..3.
 hipError_t launch_wgrad4(const bf16_t* const U[4], const bf16_t* V, int64_t N, float* partial, int grid,
                          hipStream_t s);

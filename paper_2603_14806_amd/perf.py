@@ -41,13 +41,15 @@ PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 
 
 def backward_layer_work(N, c_z=128, c=128, recompute=True):
-    """One direction of the layer backward as the library runs it: the MFMA
-    flops of its N^3 products (the recomputed forward contraction unless the
-    forward's state is passed in, dA and dB) and the algorithmic HBM bytes of
-    its per-pair kernels (per pair: projection recompute 768 B (recompute
-    only), epilogue backward 3072 B, projection backward 3328 B, six
-    weight-gradient sums 6 x 512 B = 10240 B at c_z = c = 128 with the
-    recompute; the products read their transposed operands in place)."""
+    """One direction of the layer backward: the MFMA flops of its N^3 products
+    (the recomputed forward contraction unless the forward's state is passed
+    in, dA and dB) and the HBM bytes of its per-pair kernels in the unfused
+    form, every weight-gradient operand written once and read once (per pair:
+    projection recompute 768 B (recompute only), epilogue backward 3072 B,
+    projection backward 3328 B, six weight-gradient sums 6 x 512 B = 10240 B
+    at c_z = c = 128 with the recompute; the products read their transposed
+    operands in place).  The library sums the two weights of the epilogue in
+    place and so moves 2048 B less; the figures keep this yardstick."""
     mfma = (3 if recompute else 2) * 2.0 * N ** 3 * c
     per_pair = (c_z * 2 + 2 * c * 2 if recompute else 0) \
         + (c * 4 + c_z * 2 + c_z * 4 + c * 2 + c_z * 4 + 4 * 2 * c) \
