@@ -278,7 +278,7 @@ int tri_mul_block_accumulate_packed(tri_mul_handle_t h, const tri_mul_block_view
  *     output rows [col0, col0 + cols), and likewise b the b-panel for output
  *     columns [col0, col0 + cols) (Eq. 3 contracts the first token index).
  *   a_panel, b_panel: tri_mul_block_panel_size(m, klen) bytes each, 16-byte
- *   aligned.  Uses the handle's staging buffer: one stream per handle.
+ *   aligned.
  * tri_mul_block_accumulate_blocked: the ring step of
  *   tri_mul_block_accumulate_packed with the two panels given directly in the
  *   blocked layout (a_panel: m = rows, b_panel: m = cols, both klen; the mask

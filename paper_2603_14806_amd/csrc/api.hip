@@ -877,10 +877,7 @@ int tri_mul_block_project(tri_mul_handle_t h, const void* z_tile, int64_t ld_z, 
     // (outgoing) or its columns and rows (incoming)
     const bool in = direction == TRI_MUL_INCOMING;
     const int64_t m0 = in ? col0 : row0, M = in ? cols : rows, k0 = in ? row0 : col0, K = in ? rows : cols;
-    hipError_t e = trimul::launch_stage_tile_mask(mask, m0, M, k0, K, h->w.kmask_pad, s);
-    if (e == hipSuccess)
-        e = trimul::launch_project_mfma(h->w, z_tile, ld_z, h->w.kmask_pad, (K + 31) / 32 * 32, M, K, in ? 1 : 0,
-                                        a_panel, b_panel, s);
+    const hipError_t e = trimul::launch_project_mfma(h->w, z_tile, ld_z, mask, m0, k0, M, K, in ? 1 : 0, a_panel, b_panel, s);
     if (e != hipSuccess) return hip_fail(e, "projection kernel launch");
     return ok();
 }

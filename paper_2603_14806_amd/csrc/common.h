@@ -145,11 +145,10 @@ __device__ __forceinline__ void lds_load16(v4i_t r, uint32_t voff, uint32_t soff
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
-__device__ __forceinline__ void lds_load4(v4i_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
+// One byte per lane, zero-extended: lane i writes 4 bytes at LDS address lds + 4 i.
+__device__ __forceinline__ void lds_load_u8(v4i_t r, uint32_t voff, uint32_t lds) {
     lds = __builtin_amdgcn_readfirstlane(lds);
-    soff = __builtin_amdgcn_readfirstlane(soff);
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ubyte %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 

@@ -584,19 +584,6 @@ void k2_contract_f32(const float* __restrict__ A, const float* __restrict__ B, f
         }
 }
 
-// Token mask of a tile's columns (0/1 bytes, zero from cols to cpad) followed
-// by its rows (from byte cpad, zero from rows to rpad).
-__global__ void k_stage_tile_mask(const uint8_t* __restrict__ mask, int64_t row0, int rows, int64_t col0, int cols,
-                                  int cpad, int rpad, uint8_t* __restrict__ dst) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < cpad) {
-        dst[k] = (k < cols && (!mask || mask[col0 + k] != 0)) ? 1 : 0;
-    } else if (k < cpad + rpad) {
-        const int r = k - cpad;
-        dst[k] = (r < rows && (!mask || mask[row0 + r] != 0)) ? 1 : 0;
-    }
-}
-
 __global__ void k_stage_kmask(const uint8_t* __restrict__ mask, int klen, int padded, uint8_t* __restrict__ dst) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k < padded) dst[k] = (k < klen && (!mask || mask[k] != 0)) ? 1 : 0;
@@ -669,10 +656,14 @@ bool cblocked_fits(int64_t N, int batch) {
 
 // Pacing needs whole XCD groups (G a multiple of 8, all resident) and at
 // least two full rounds; it resets the counters first (a kernel, not a
-// memset, so that the sequence can be captured in a graph).
+// memset, so that the sequence can be captured in a graph).  It pays only for
+// long tiles: shorter ones drift apart less than the wait and the reset cost
+// (N = 4096 13.67 ms paced, 13.96 not; N = 2048 1954 against 1910 us, N = 1300
+// 695 against 649, N = 512 55 against 51).
+constexpr int64_t kPaceMinK = 3072;
 namespace {
-int pace_launch(int grid, int total, hipStream_t s) {
-    if ((grid & 7) != 0 || total < 2 * grid) return 0;
+int pace_launch(int grid, int total, int64_t K, hipStream_t s) {
+    if ((grid & 7) != 0 || total < 2 * grid || K < kPaceMinK) return 0;
     hipLaunchKernelGGL(k_pace_reset, dim3(1), dim3(8 * kPaceLine), 0, s);
     return 1;
 }
@@ -684,7 +675,7 @@ hipError_t launch_contract_blocked_rowc(const void* A, const void* B, float* C, 
     const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
     const int total = tm * tn * batch;
     const int grid = total < cus ? total : cus;
-    const int pace = pace_launch(grid, total, s);
+    const int pace = pace_launch(grid, total, K, s);
     hipLaunchKernelGGL((k2_contract_ws<true, false, false>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A,
                        (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, N, (int64_t)0, (int64_t)0, M * N, tm, tn,
                        total, accumulate, (const uint8_t*)nullptr, pace);
@@ -698,7 +689,7 @@ hipError_t launch_contract_blocked_packed(const void* A, const void* B, float* C
     const int total = tm * tn * batch;
     const int grid = total < cus ? total : cus;
     if (!cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, s);
+    const int pace = pace_launch(grid, total, K, s);
     hipLaunchKernelGGL((k2_contract_ws<true, false, true>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A,
                        (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, (int64_t)0, (int64_t)0, (int64_t)0,
                        (int64_t)0, tm, tn, total, accumulate, (const uint8_t*)nullptr, pace);
@@ -712,7 +703,7 @@ hipError_t launch_contract_transposed(int ta, int tb, const void* A, const void*
     const int total = tm * tn * batch;
     const int grid = total < cus ? total : cus;
     if ((!ta && !tb) || !cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, s);
+    const int pace = pace_launch(grid, total, K, s);
 #define K2_TR(TA_, TB_)                                                                                             \
     hipLaunchKernelGGL((k2_contract_ws<true, false, true, TA_, TB_>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A, \
                        (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, (int64_t)0, (int64_t)0, (int64_t)0,     \
@@ -721,14 +712,6 @@ hipError_t launch_contract_transposed(int ta, int tb, const void* A, const void*
     else if (ta && tb) K2_TR(true, true);
     else K2_TR(true, false);
 #undef K2_TR
-    return hipGetLastError();
-}
-
-hipError_t launch_stage_tile_mask(const uint8_t* mask, int64_t row0, int64_t rows, int64_t col0, int64_t cols,
-                                  uint8_t* dst, hipStream_t s) {
-    const int cpad = (int)((cols + 31) / 32 * 32), rpad = (int)((rows + 3) / 4 * 4);
-    hipLaunchKernelGGL(k_stage_tile_mask, dim3((unsigned)((cpad + rpad + 255) / 256)), dim3(256), 0, s, mask, row0,
-                       (int)rows, col0, (int)cols, cpad, rpad, dst);
     return hipGetLastError();
 }
 
@@ -770,7 +753,7 @@ hipError_t launch_contract(int dtype, int blocked, const void* A, const void* B,
     const bf16_t* a = (const bf16_t*)A;
     const bf16_t* b = (const bf16_t*)B;
     if (blocked && !cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, s);
+    const int pace = pace_launch(grid, total, K, s);
 #define K2_WS(BL, KM)                                                                                              \
     hipLaunchKernelGGL((k2_contract_ws<BL, KM, BL>), dim3(grid), dim3(768), 0, s, a, b, C, (int)M, (int)N, (int)K, \
                        (int)lda, (int)ldb, ldc, sA, sB, sC, tm, tn, total, accumulate, kmask, pace)

@@ -392,17 +392,16 @@ void k3_epilogue_mfma(EpilogueArgs a, int nchunk, int64_t nunits, const bf16_t* 
 //                   afterwards y_hi [0, 8192) and y_lo [8192, 16384)
 //   [16384, 24576)  z of the unit, [32 pairs][128] bf16: chunk q of pair row p
 //                   at slot q ^ (p & 1); afterwards x_hi
-//   [24576, 25600)  per-wave mask bytes: column mask bytes j0 .. j0 + 31 at 0,
-//                   the dword of row mask byte i at 32 (0/1 bytes staged by
-//                   launch_stage_tile_mask: columns, zero past cols, then rows
-//                   from byte rmoff)
+//   [24576, 25600)  per-wave mask bytes, one per dword: columns j0 .. j0 + 31,
+//                   then row i (straight from the caller's mask, the columns'
+//                   at coff, the rows' at roff)
 constexpr int kRC = 16384, kRZ = 8192, kRM = 1024;
 constexpr int kRSt = kRC + kRZ + kRM;
 
 template <typename TO>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z, const uint8_t* __restrict__ tmask,
-                      int rows, int cols, int rmoff, int nunits, TO* __restrict__ out, const bf16_t* __restrict__ wepi,
+void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z, const uint8_t* __restrict__ mask,
+                      uint32_t coff, uint32_t roff, uint32_t mrange, int cols, int nunits, TO* __restrict__ out, const bf16_t* __restrict__ wepi,
                       const float* __restrict__ lnin_w, const float* __restrict__ lnin_b,
                       const float* __restrict__ lnout_w, const float* __restrict__ lnout_b, float eps) {
     // fp32 output leaves straight from the accumulators (a register holds 32
@@ -438,7 +437,6 @@ void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z,
     const int drow = w * 8 + (lane >> 4);
     const uint32_t dchunk = (uint32_t)(((lane & 15) ^ (drow & 1)) << 4);
     const uint32_t dv0 = (uint32_t)drow * kYRow + dchunk, dv1 = (uint32_t)(drow + 4) * kYRow + dchunk;
-    const uint32_t mpad = (uint32_t)rmoff + (uint32_t)((rows + 3) / 4 * 4);   // staged mask bytes
     auto decode = [&](int u, int& i, int& j0) {
         i = u / nchunk;
         j0 = (u - i * nchunk) * kP3;
@@ -455,9 +453,9 @@ void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z,
         const v4i_t rz = buffer_desc(z + ((int64_t)i * cols + j0) * kCz, (uint32_t)np * kYRow);
         lds_load16(rz, dv0, 0, st + kRC + w * 2048);
         lds_load16(rz, dv1, 0, st + kRC + w * 2048 + 1024);
-        const v4i_t rm = buffer_desc(tmask, valid ? mpad : 0u);
-        const uint32_t mo = lane < 8 ? (uint32_t)(j0 + 4 * lane) : lane == 8 ? (uint32_t)(rmoff + (i & ~3)) : 0xfffffff0u;
-        lds_load4(rm, mo, 0, st + kRC + kRZ + w * 256);
+        const v4i_t rm = buffer_desc(mask, valid ? mrange : 0u);
+        const uint32_t mo = lane < 32 ? coff + (uint32_t)(j0 + lane) : lane == 32 ? roff + (uint32_t)i : 0xfffffff0u;
+        lds_load_u8(rm, mo, st + kRC + kRZ + w * 256);
     };
     issue(first, 0);
     if (kStages == 3) issue(first + G, 1);
@@ -518,12 +516,12 @@ void k3_epilogue_ring(const float* __restrict__ C, const bf16_t* __restrict__ z,
                 zv[2 * k + 1] = __uint_as_float(uu[k] & 0xffff0000u);
             }
         }
-        const uint8_t* ms = reinterpret_cast<const uint8_t*>(st + kRC + kRZ + w * 256);
+        const uint32_t* ms = reinterpret_cast<const uint32_t*>(st + kRC + kRZ + w * 256);
         int ui, uj0;
         decode(u, ui, uj0);
-        // Masked pairs (and tail pairs, whose staged mask is zero) get y = 0:
-        // W_o y, and so the output, is then exactly 0 (no bias).
-        const uint32_t keep = (ms[lp] & ms[32 + (ui & 3)]) ? 0xffffffffu : 0u;
+        // Masked pairs (and tail pairs) get y = 0: W_o y, and so the output, is
+        // then exactly 0 (no bias).
+        const uint32_t keep = uj0 + lp < cols && (!mask || (ms[lp] != 0 && ms[32] != 0)) ? 0xffffffffu : 0u;
         __syncthreads();   // every thread has read its C and z; the stage becomes y_hi, y_lo, x_hi
 
         {
@@ -654,12 +652,12 @@ hipError_t launch_mfma(const DeviceWeights& w, const EpilogueArgs& a, hipStream_
     const unsigned g = (unsigned)(nunits < cap ? nunits : cap);
     const bool vec = (a.ldc % 4) == 0 && (a.sc % 4) == 0 && (reinterpret_cast<uintptr_t>(a.C) & 15u) == 0;
     if (a.cblocked) {   // C in the pair-blocked layout: the full update, or a tile's packed accumulator
-        const int rmoff = (int)((a.cols + 31) / 32 * 32);
-        hipError_t e = launch_stage_tile_mask(a.mask, a.row0, a.rows, a.col0, a.cols, w.kmask_pad, s);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k3_epilogue_ring<TO>), dim3(g), dim3(256), 0, s, a.C, (const bf16_t*)a.z, w.kmask_pad,
-                           (int)a.rows, (int)a.cols, rmoff, (int)nunits, (TO*)a.out, w.epi_bf, w.ln_in_w, w.ln_in_b,
-                           w.ln_out_w, w.ln_out_b, w.eps);
+        const int64_t lo = a.row0 < a.col0 ? a.row0 : a.col0;   // the mask bytes read start here
+        const uint32_t coff = (uint32_t)(a.col0 - lo), roff = (uint32_t)(a.row0 - lo);
+        const uint32_t ce = coff + (uint32_t)a.cols, re = roff + (uint32_t)a.rows;
+        hipLaunchKernelGGL((k3_epilogue_ring<TO>), dim3(g), dim3(256), 0, s, a.C, (const bf16_t*)a.z,
+                           a.mask ? a.mask + lo : nullptr, coff, roff, a.mask ? (ce > re ? ce : re) : 0u, (int)a.cols,
+                           (int)nunits, (TO*)a.out, w.epi_bf, w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
     } else if (vec)
         hipLaunchKernelGGL((k3_epilogue_mfma<TO, true, false>), dim3(g), dim3(256), 0, s, a, nchunk, nunits, w.epi_bf,
                            w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);

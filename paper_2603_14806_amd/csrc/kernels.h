@@ -40,20 +40,15 @@ struct DeviceWeights {
     } k1s{};
     float eps = 1e-5f;
     int cus = 256;                // compute units of the device (persistent grids)
-    uint8_t* kmask_pad = nullptr; // 0/1 staging of a token mask (k-panel, sequence, or a tile's columns and rows), kMaskStageBytes
+    uint8_t* kmask_pad = nullptr; // 0/1 staging of a k-panel's token mask, kMaskStageBytes
 };
 
 constexpr int64_t kMaxKPanel = 65536;   // longest k-panel of one block call
-constexpr int64_t kMaskStageBytes = 2 * kMaxKPanel + 128;   // size of DeviceWeights::kmask_pad
+constexpr int64_t kMaskStageBytes = kMaxKPanel + 128;   // size of DeviceWeights::kmask_pad
 
 // Copies mask[0, klen) into dst as 0/1 bytes (mask NULL: all ones) and zero-fills dst up to the next
 // multiple of 32 (so the contraction can read whole 4-byte words of it).
 hipError_t launch_stage_kmask(const uint8_t* mask, int64_t klen, uint8_t* dst, hipStream_t s);
-// Stages a tile's token mask for the epilogue: dst[0, ceil(cols/32)*32) = 0/1 of mask[col0 + k] (zero
-// past cols), then dst[ceil(cols/32)*32 + r] = 0/1 of mask[row0 + r] for r < ceil(rows/4)*4 (zero past
-// rows); mask NULL: all ones.  dst must hold kMaskStageBytes.
-hipError_t launch_stage_tile_mask(const uint8_t* mask, int64_t row0, int64_t rows, int64_t col0, int64_t cols,
-                                  uint8_t* dst, hipStream_t s);
 // Row-major bf16 panel [nch][rows][ld] -> blocked [nch][ceil(rows/256)][ceil(klen/32)][256][32],
 // staged k-mask applied, padding zero.
 hipError_t launch_panel_block(const void* P, int64_t rows, int64_t ld, int64_t klen, int nch, const uint8_t* kst,
@@ -108,11 +103,10 @@ struct EpilogueArgs {
 // left untouched; the k padding of a row's last k-step is written with zeros.
 // The bf16 projection of an M x K operand pair (A, B in the blocked layout of
 // panel_geom(M, K)): operand row i, contraction index k is pair (i, k) of z
-// (outgoing) or (k, i) (incoming), z rows ldz pairs apart; tmask holds the
-// staged 0/1 bytes of the k-range at [0, ceil(K/32)*32) and of operand row i
-// at rmoff + i.
-hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ldz, const uint8_t* tmask, int64_t rmoff,
-                               int64_t M, int64_t K, int incoming, void* A, void* B, hipStream_t s);
+// (outgoing) or (k, i) (incoming), z rows ldz pairs apart; mask: token mask
+// over global indices or null, operand row i's byte at m0 + i, k's at k0 + k.
+hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ldz, const uint8_t* mask, int64_t m0,
+                               int64_t k0, int64_t M, int64_t K, int incoming, void* A, void* B, hipStream_t s);
 hipError_t launch_project(int dtype, const DeviceWeights& w, const void* z, const uint8_t* mask,
                           int64_t N, int incoming, void* A, void* B, hipStream_t s);
 

@@ -169,13 +169,12 @@ __device__ __forceinline__ uint32_t xoff(int p, int chunk) {
 // The operands are M x K: operand row i (M of them) and contraction index k
 // (K).  Outgoing, pair (i, k) is z[i][k]; incoming, pair (k, i) is z[k][i];
 // z rows are ldz pairs apart (the full update: M = K = ldz = N; a device
-// tile: its rows and columns).  tmask: the staged 0/1 token bytes, the
-// k-range's at [0, ceil(K/32)*32) (zero past K) and operand row i's at
-// rmoff + i; mrange bytes of it are readable.
+// tile: its rows and columns).  mask: token bytes (null: all real), the
+// k-range's at koff, the operand rows' at roff; mrange bytes are readable.
 template <bool INCOMING>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __restrict__ tmask, int rmoff,
-                     int mrange, int M, int K, int nlines, const uint16_t* __restrict__ wproj,
+void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __restrict__ mask, uint32_t koff,
+                     uint32_t roff, uint32_t mrange, int M, int K, int nlines, const uint16_t* __restrict__ wproj,
                      const float* __restrict__ lnw, const float* __restrict__ lnb, float eps,
                      DeviceWeights::K1Scales ks, bf16_t* __restrict__ A, bf16_t* __restrict__ B) {
     __shared__ __attribute__((aligned(16))) char ring[kRing * kSt];     // z rows [p][256 B], mask
@@ -198,9 +197,9 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
     // chunk q sits at slot q ^ (p & 1), so that the LayerNorm reads of two
     // neighbouring rows hit disjoint banks.  Wave g loads rows 8 g .. 8 g + 7
     // (two 1 KB loads: lane i -> row 8 g + 4 h + i / 16, slot i % 16) and its
-    // own copy of the line's mask bytes: m[k0 .. k0 + 31] at 0, the dword of
-    // row r's byte at 32.  Lines past the end load nothing (zero-size
-    // descriptor).
+    // own copy of the line's mask bytes, one per dword: pairs k0 .. k0 + 31,
+    // then row r (straight from the caller's mask: staging it took a launch of
+    // its own, 5 us).  Lines past the end load nothing (zero-size descriptor).
     const uint32_t zstep = INCOMING ? (uint32_t)ldz * kXRow : (uint32_t)kXRow;   // bytes between pairs
     const uint32_t ring_base = lds_addr(ring);
     const int drow = g * 8 + (lane >> 4);
@@ -220,9 +219,9 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
         const uint32_t st = ring_base + (uint32_t)(stage * kSt);
         lds_load16(rz, dv0, 0, st + g * 2048);
         lds_load16(rz, dv1, 0, st + g * 2048 + 1024);
-        const v4i_t rm = buffer_desc(tmask, valid ? (uint32_t)mrange : 0u);
-        const uint32_t mo = lane < 8 ? (uint32_t)(k0 + 4 * lane) : lane == 8 ? (uint32_t)(rmoff + (r & ~3)) : 0xfffffff0u;
-        lds_load4(rm, mo, 0, st + kZSt + g * 256);
+        const v4i_t rm = buffer_desc(mask, valid ? mrange : 0u);
+        const uint32_t mo = lane < 32 ? koff + (uint32_t)(k0 + lane) : lane == 32 ? roff + (uint32_t)r : 0xfffffff0u;
+        lds_load_u8(rm, mo, st + kZSt + g * 256);
     };
     issue(first, 0);
     issue(first + G, 1);
@@ -293,12 +292,12 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
         f16x8_t xh[2];
 #pragma unroll
         for (int i = 0; i < 16; ++i) xh[i >> 3][i & 7] = (_Float16)(v[i] * rs * gam[i] + bet[i]);
-        // A masked pair (and a ragged line's tail: the staged mask is zero
-        // past K) gets x = 0, so W x and with it a and b are exactly 0; the
-        // AND also clears what a NaN in z would have left.
+        // A masked pair (and a ragged line's tail past K) gets x = 0, so W x
+        // and with it a and b are exactly 0; the AND also clears what a NaN in
+        // z would have left.
         const int kc = line / M, r0 = line - kc * M, k0 = kc * kP1;
-        const uint8_t* ms = reinterpret_cast<const uint8_t*>(zs + kZSt + g * 256);   // this wave's copy
-        const uint32_t keep = (ms[lp] & ms[32 + (r0 & 3)]) ? 0xffffffffu : 0u;
+        const uint32_t* ms = reinterpret_cast<const uint32_t*>(zs + kZSt + g * 256);   // this wave's copy
+        const uint32_t keep = k0 + lp < K && (!mask || (ms[lp] != 0 && ms[32] != 0)) ? 0xffffffffu : 0u;
         uint4 x0 = __builtin_bit_cast(uint4, xh[0]), x1 = __builtin_bit_cast(uint4, xh[1]);
         x0 = make_uint4(x0.x & keep, x0.y & keep, x0.z & keep, x0.w & keep);
         x1 = make_uint4(x1.x & keep, x1.y & keep, x1.z & keep, x1.w & keep);
@@ -353,20 +352,23 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
 
 }  // namespace
 
-hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ldz, const uint8_t* tmask, int64_t rmoff,
-                               int64_t M, int64_t K, int incoming, void* A, void* B, hipStream_t s) {
+hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ldz, const uint8_t* mask, int64_t m0,
+                               int64_t k0, int64_t M, int64_t K, int incoming, void* A, void* B, hipStream_t s) {
     const int nch = (int)((K + kP1 - 1) / kP1);
     const int nlines = (int)(M * nch);
     const unsigned g = (unsigned)(nlines < 2 * w.cus ? nlines : 2 * w.cus);
-    const int mrange = (int)std::max((K + 31) / 32 * 32, rmoff + (M + 3) / 4 * 4);
+    const int64_t lo = std::min(m0, k0);   // the mask bytes read start here
+    const uint32_t koff = (uint32_t)(k0 - lo), roff = (uint32_t)(m0 - lo);
+    const uint8_t* mk = mask ? mask + lo : nullptr;
+    const uint32_t mrange = mask ? std::max(koff + (uint32_t)K, roff + (uint32_t)M) : 0u;
     if (incoming)
-        hipLaunchKernelGGL((k1_project_mfma<true>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, tmask,
-                           (int)rmoff, mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps,
-                           w.k1s, (bf16_t*)A, (bf16_t*)B);
+        hipLaunchKernelGGL((k1_project_mfma<true>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, mk, koff, roff,
+                           mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps, w.k1s,
+                           (bf16_t*)A, (bf16_t*)B);
     else
-        hipLaunchKernelGGL((k1_project_mfma<false>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, tmask,
-                           (int)rmoff, mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps,
-                           w.k1s, (bf16_t*)A, (bf16_t*)B);
+        hipLaunchKernelGGL((k1_project_mfma<false>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, mk, koff, roff,
+                           mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps, w.k1s,
+                           (bf16_t*)A, (bf16_t*)B);
     return hipGetLastError();
 }
 
@@ -383,9 +385,7 @@ hipError_t launch_project(int dtype, const DeviceWeights& w, const void* z, cons
                                w.ln_in_w, w.ln_in_b, w.eps, (float*)A, (float*)B);
         return hipGetLastError();
     }
-    hipError_t e = launch_stage_kmask(mask, N, w.kmask_pad, s);
-    if (e != hipSuccess) return e;
-    return launch_project_mfma(w, z, N, w.kmask_pad, 0, N, N, incoming, A, B, s);
+    return launch_project_mfma(w, z, N, mask, 0, 0, N, N, incoming, A, B, s);
 }
 
 }  // namespace trimul
