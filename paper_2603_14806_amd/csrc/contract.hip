@@ -8,6 +8,7 @@
 // panels arrive unmasked).  The bf16 path runs on gfx950 matrix cores
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulation), and so does the fp32 path
 // (v_mfma_f32_32x32x2_f32).
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -104,11 +105,16 @@ __global__ void k_pace_reset() {
     if (threadIdx.x < 8 * kPaceLine) g_k2_pace[threadIdx.x] = 0u;
 }
 
-template <bool BLOCKED, bool KMASK, bool CBLOCKED, bool TA = false, bool TB = false>
+// RAGGED: tiles of one to four units a side (k2_addr.h); without it every tile
+// is whole.  (One more instance of the tile loop per shape costs whole tiles
+// about 1%, so launches that have only those run without it.)  Ragged tiles
+// took the contraction from 34.0 to 32.0 us at N = 384 (3 + 3 units), from
+// 28.2 to 25.3 at N = 300 and from 676 to 646 at N = 1300.
+template <bool BLOCKED, bool KMASK, bool CBLOCKED, bool TA, bool TB, bool RAGGED>
 __global__ __attribute__((amdgpu_flat_work_group_size(768, 768), amdgpu_waves_per_eu(3, 3)))
 void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, float* __restrict__ C, int M,
-                    int N, int K, int lda, int ldb, int64_t ldc, int64_t sA, int64_t sB, int64_t sC, int tiles_m,
-                    int tiles_n, int total, int accumulate, const uint8_t* __restrict__ kmask, int pace) {
+                    int N, int K, int lda, int ldb, int64_t ldc, int64_t sA, int64_t sB, int64_t sC, int total,
+                    int accumulate, const uint8_t* __restrict__ kmask, int pace) {
     constexpr int BM = kK2Tile, MI = 2;
     constexpr int A_ST = BM * ROWB, ST_BYTES = A_ST + B_ST;
     constexpr int STAGES = kLdsBytes / ST_BYTES;  // 5
@@ -124,8 +130,15 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
     const int my_tiles = k2_my_tiles(perm, G, total);
     const int nk = (K + BK - 1) / BK;
     const int steps = my_tiles * nk;
-    const int tiles = tiles_m * tiles_n;
-    const int nchan = total / tiles;
+    const K2Side sm = k2_side(TA ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, M);
+    const K2Side sn = k2_side(TB ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, N);
+    const int nchan = total / (sm.tiles * sn.tiles);
+    auto decode = [&](int L) -> K2Tile {
+        if constexpr (RAGGED) return k2_decode(sm, sn, L);
+        int ch, ti, tj;
+        k2_index(sm, sn, L, ch, ti, tj);
+        return K2Tile{ch, ti * kK2Tile, tj * kK2Tile, 4, 4};
+    };
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // 0 .. 11
@@ -139,7 +152,7 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
         const K2Operand opa{TA ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, M, K, lda, sA};
         const K2Operand opb{TB ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, N, K, ldb, sB};
         const uint32_t la = k2_lane_off(opa, lw, lane), lb = k2_lane_off(opb, lw, lane);
-        int l_it = 0, l_kt = 0, l_stage = 0, l_ch = 0, l_m0 = 0, l_n0 = 0;
+        int l_it = 0, l_kt = 0, l_stage = 0, l_ch = 0, l_m0 = 0, l_n0 = 0, l_mu = 4, l_nu = 4;
         const v4i_t rnone = buffer_desc(A, 0u);
         v4i_t ra = rnone, rb = rnone;
         auto desc = [&](const bf16_t* X, const K2Operand& op, int t0, int kt) {
@@ -159,10 +172,11 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
                     __builtin_amdgcn_s_sleep(1);
                 }
             }
-            const K2Tile tl = k2_decode(l_it * G + perm, tiles_m, tiles_n);
+            const K2Tile tl = decode(l_it * G + perm);
             l_ch = tl.ch;
             l_m0 = tl.m0;
             l_n0 = tl.n0;
+            if (RAGGED) l_mu = tl.mu, l_nu = tl.nu;
             if (!TA) ra = desc(A, opa, l_m0, 0);
             if (!TB) rb = desc(B, opb, l_n0, 0);
         };
@@ -174,7 +188,7 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
                 const bool isb = j >= kK2LoadsPerOperand;
                 const int jj = j % kK2LoadsPerOperand;
                 uint32_t off;
-                const bool in = k2_load_off(isb ? opb : opa, isb ? l_n0 : l_m0, l_kt, lw, jj, off);
+                const bool in = k2_load_off(isb ? opb : opa, isb ? l_n0 : l_m0, RAGGED ? (isb ? l_nu : l_mu) : 4, l_kt, lw, jj, off);
                 const uint32_t dst = st + (isb ? A_ST : 0) + k2_lds_off(lw, jj);
                 lds_load16((live && in) ? (isb ? rtb : rta) : rnone, (isb ? lb : la) + off, 0u, dst);
             }
@@ -269,44 +283,23 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
         return;
     }
 
-    const int wm = wave >> 1, wn = wave & 1;                   // rows 64 wm, columns 128 wn
     // The matrix-core waves issue ahead of the loader wave that shares their
     // SIMD (instruction-issue priority inside the work-group; 1% faster than
     // equal priority, the reverse 0.5% slower).
     __builtin_amdgcn_s_setprio(1);
     const int rl = lane & 31, hi = lane >> 5;
     const int q = (rl >> 2) & 3;
-    uint32_t rdA[2], rdB[2];
+    uint32_t rd[2];   // plain operand: this lane's row of a 32-row block, sub-step 0 and 1
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-        const uint32_t x = (uint32_t)(((2 * sub + hi) ^ q) << 4);
-        rdA[sub] = (wm * 64 + rl) * ROWB + x;
-        rdB[sub] = A_ST + (wn * 128 + rl) * ROWB + x;
-    }
+    for (int sub = 0; sub < 2; ++sub) rd[sub] = (uint32_t)(rl * ROWB + (((2 * sub + hi) ^ q) << 4));
     // transposed operands: this lane's address in a column block
     const int tg = lane >> 4;
     const uint32_t trb = (uint32_t)((8 * (tg >> 1) + ((lane >> 2) & 3)) * ROWB + (16 * (tg & 1) + 4 * (lane & 3)) * 2);
-    // operand i (A) / j (B) of sub-step sub from the stage at st
-    auto opA = [&](const char* st, int sub, int i) -> bf16x8_t {
-        if constexpr (TA) return lds_read_tr8(st + trb + (2 * wm + i) * 2048 + sub * 16 * ROWB);
-        else return *reinterpret_cast<const bf16x8_t*>(st + rdA[sub] + i * 32 * ROWB);
-    };
-    auto opB = [&](const char* st, int sub, int j) -> bf16x8_t {
-        if constexpr (TB) return lds_read_tr8(st + A_ST + trb + (4 * wn + j) * 2048 + sub * 16 * ROWB);
-        else return *reinterpret_cast<const bf16x8_t*>(st + rdB[sub] + j * 32 * ROWB);
-    };
     // Pair-blocked C (CBLOCKED): descriptors and offsets from k2_addr.h
     // (rows past M fall outside a block's descriptor: loads read 0, stores
     // are dropped).
     const uint32_t crs = k2_c_row_floats(N, nchan);
     const uint32_t cvo = k2_c_lane_off(crs, lane);
-    auto cdesc = [&](const K2Tile& tl, __amdgpu_buffer_rsrc_t* rc) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const K2Desc d = k2_c_desc(M, N, nchan, tl, wave, j);
-            rc[j] = make_rsrc(C + d.base, d.range);
-        }
-    };
     // byte offset of register r of 32 x 32 block x from the lane's base vo.
     // Each use site passes a fresh copy of the base (opaque to the
     // compiler), so that the 32 row offsets are formed where they are used
@@ -318,28 +311,59 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
         return v;
     };
     int c_stage = 0;
-    for (int it = 0; it < my_tiles; ++it) {
-        bf16x8_t a0[MI], b0[4];  // sub-step 0 operands, read one step ahead within a tile
-        f32x16_t acc[MI][4];
+    // One tile of NI x NJ blocks for this wave (NI = 0: it only keeps the
+    // barriers).
+    auto tile = [&](const K2Tile& tl, auto ni, auto nj) {
+        constexpr int NI = decltype(ni)::value, NJ = decltype(nj)::value;
+        if constexpr (NI == 0) {
+            for (int kt = 0; kt < nk; ++kt) {
+                __syncthreads();
+                c_stage = c_stage == STAGES - 1 ? 0 : c_stage + 1;
+            }
+        } else {
+        const K2Wave wv = RAGGED ? k2_wave(tl, wave) : K2Wave{2 * (wave >> 1), 2, 4 * (wave & 1), 4};
+        // this lane's address of operand block i (A) / j (B) of the wave in the
+        // stage at st, sub-step sub (2 KB per 32-row block in either layout)
+        const uint32_t oa[2] = {(TA ? trb : rd[0]) + wv.rb * 2048, (TA ? trb + 16 * ROWB : rd[1]) + wv.rb * 2048};
+        const uint32_t ob[2] = {(TB ? trb : rd[0]) + A_ST + wv.cb * 2048, (TB ? trb + 16 * ROWB : rd[1]) + A_ST + wv.cb * 2048};
+        auto opA = [&](const char* st, int sub, int i) -> bf16x8_t {
+            if constexpr (TA) return lds_read_tr8(st + oa[0] + i * 2048 + sub * 16 * ROWB);
+            else return *reinterpret_cast<const bf16x8_t*>(st + oa[sub] + i * 2048);
+        };
+        auto opB = [&](const char* st, int sub, int j) -> bf16x8_t {
+            if constexpr (TB) return lds_read_tr8(st + ob[0] + j * 2048 + sub * 16 * ROWB);
+            else return *reinterpret_cast<const bf16x8_t*>(st + ob[sub] + j * 2048);
+        };
+        auto cdesc = [&](__amdgpu_buffer_rsrc_t* rc) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const K2Desc d = k2_c_desc(M, N, nchan, tl, wv, j);
+                rc[j] = make_rsrc(C + d.base, d.range);
+            }
+        };
+        bf16x8_t a0[NI], b0[NJ];  // sub-step 0 operands, read one step ahead within a tile
+        f32x16_t acc[NI][NJ];
         if (CBLOCKED && accumulate) {
-            // accumulating: the accumulators start from C, all 128 loads
-            // issued together and waited for once (one HBM round trip per
-            // tile instead of one per 32 x 32 block at the end)
-            __amdgpu_buffer_rsrc_t rc[4];
-            cdesc(k2_decode(it * G + perm, tiles_m, tiles_n), rc);
+            // accumulating: the accumulators start from C, all loads issued
+            // together and waited for once (one HBM round trip per tile
+            // instead of one per 32 x 32 block at the end)
+            __amdgpu_buffer_rsrc_t rc[NJ];
+            cdesc(rc);
             const uint32_t vo = fresh(cvo);
 #pragma unroll
-            for (int x = 0; x < 4 * MI; ++x)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[x >> 2][x & 3][r] =
-                        __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc[x & 3], coff(vo, x, r), 0, 0));
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        acc[i][j][r] = __builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(rc[j], coff(vo, 4 * i + j, r), 0, 0));
             wait_vmcnt_pinned<0>();
         } else {
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
         }
@@ -347,89 +371,120 @@ void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, 
         // a tile's first step: barrier, then its sub-step 0 operands (nothing
         // is read ahead across the C stores)
         __syncthreads();
+        {
+            const char* st = smem + c_stage * ST_BYTES;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            b0[j] = opB(smem + c_stage * ST_BYTES, 0, j);
+            for (int j = 0; j < NJ; ++j) b0[j] = opB(st, 0, j);
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-            a0[i] = opA(smem + c_stage * ST_BYTES, 0, i);
+            for (int i = 0; i < NI; ++i) a0[i] = opA(st, 0, i);
+        }
         for (int kt = 0; kt < nk; ++kt) {
             if (kt > 0) __syncthreads();
             const char* st = smem + c_stage * ST_BYTES;
             c_stage = c_stage == STAGES - 1 ? 0 : c_stage + 1;
             const char* stn = smem + c_stage * ST_BYTES;             // the next step
-            bf16x8_t a1[MI], b1[4];
+            bf16x8_t a1[NI], b1[NJ];
+            // sub-step 0; the operand reads of sub-step 1 start after its
+            // first two MFMAs (what is left of them comes after the last)
 #pragma unroll
-            for (int x = 0; x < 4 * MI; ++x) {
-                const int i = x >> 2, j = x & 3;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i], b0[j], acc[i][j], 0, 0, 0);
-                const int y = x - 2;   // reads of sub-step 1 start after the first two MFMAs
-                if (y >= 0 && y < 4) b1[y] = opB(st, 1, y);
-                else if (y >= 4 && y < 4 + MI) a1[y - 4] = opA(st, 1, y - 4);
+            for (int x = 0; x < NI * NJ + NI + NJ; ++x) {
+                const int i = x / NJ, j = x % NJ, y = x - 2;
+                if (x < NI * NJ) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[i], b0[j], acc[i][j], 0, 0, 0);
+                if (y >= 0 && y < NJ) b1[y] = opB(st, 1, y);
+                else if (y >= NJ && y < NJ + NI) a1[y - NJ] = opA(st, 1, y - NJ);
             }
+            if (NI * NJ + NI + NJ < 2 + NI + NJ) a1[NI - 1] = opA(st, 1, NI - 1);
             // sub-step 1; after MFMA x, the operand read x - 2 of the next
             // step's sub-step 0 (its stage is complete since this step's
             // barrier; after a tile's last step the values go unused)
 #pragma unroll
-            for (int x = 0; x < 4 * MI; ++x) {
-                const int i = x >> 2, j = x & 3;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[i], b1[j], acc[i][j], 0, 0, 0);
-                const int y = x - 2;
-                if (y >= 0 && y < 4) b0[y] = opB(stn, 0, y);
-                else if (y >= 4 && y < 4 + MI) a0[y - 4] = opA(stn, 0, y - 4);
+            for (int x = 0; x < NI * NJ + NI + NJ; ++x) {
+                const int i = x / NJ, j = x % NJ, y = x - 2;
+                if (x < NI * NJ) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[i], b1[j], acc[i][j], 0, 0, 0);
+                if (y >= 0 && y < NJ) b0[y] = opB(stn, 0, y);
+                else if (y >= NJ && y < NJ + NI) a0[y - NJ] = opA(stn, 0, y - NJ);
             }
+            if (NI * NJ + NI + NJ < 2 + NI + NJ) a0[NI - 1] = opA(stn, 0, NI - 1);
         }
 
         // 32x32 accumulator layout: lane holds column (lane & 31) and, in
         // register r, row 8 (r / 4) + 4 (lane / 32) + r % 4.
-        const K2Tile tl = k2_decode(it * G + perm, tiles_m, tiles_n);
-        const int ch = tl.ch, m0 = tl.m0, n0 = tl.n0;
-        const int row0 = m0 + wm * 64 + 4 * hi, col0 = n0 + wn * 128 + rl;
-        const bool full = m0 + BM <= M && n0 + BN <= N;
         if constexpr (CBLOCKED) {   // the sums (C included when accumulating) go straight out
-            __amdgpu_buffer_rsrc_t rc[4];
-            cdesc(tl, rc);
+            __amdgpu_buffer_rsrc_t rc[NJ];
+            cdesc(rc);
             const uint32_t vo = fresh(cvo);
 #pragma unroll
-            for (int x = 0; x < 4 * MI; ++x)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[x >> 2][x & 3][r]), rc[x & 3],
-                                                          coff(vo, x, r), 0, 0);
-            continue;
-        }
-        float* Cb = C + ch * sC + (int64_t)row0 * ldc + col0;
-        const int64_t row_step = ldc;   // elements between rows
-        // One 32 x 32 block at a time.  Accumulating, the block's 16 loads
-        // go out together (a lane outside C reads C[0] instead) and are
-        // waited for once, before its 16 guarded stores; element by element
-        // the compiler would wait for every load.
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+                    for (int r = 0; r < 16; ++r)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][r]), rc[j],
+                                                              coff(vo, 4 * i + j, r), 0, 0);
+        } else {
+            const int row0 = tl.m0 + 32 * wv.rb + 4 * hi, col0 = tl.n0 + 32 * wv.cb + rl;
+            const bool full = tl.m0 + 32 * (wv.rb + NI) <= M && tl.n0 + 32 * (wv.cb + NJ) <= N;
+            float* Cb = C + tl.ch * sC + (int64_t)row0 * ldc + col0;
+            const int64_t row_step = ldc;   // elements between rows
+            // One 32 x 32 block at a time.  Accumulating, the block's 16 loads
+            // go out together (a lane outside C reads C[0] instead) and are
+            // waited for once, before its 16 guarded stores; element by element
+            // the compiler would wait for every load.
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float* pb = Cb + j * 32;   // column block j
-                const bool colok = full || col0 + j * 32 < N;
-                float v[16];
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
-                if (accumulate) {
-                    float old[16];
+                for (int j = 0; j < NJ; ++j) {
+                    float* pb = Cb + j * 32;   // column block j
+                    const bool colok = full || col0 + j * 32 < N;
+                    float v[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
+                    if (accumulate) {
+                        float old[16];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int dr = i * 32 + 8 * (r >> 2) + (r & 3);
+                            const bool ok = colok && (full || row0 + dr < M);
+                            old[r] = *(ok ? pb + (int64_t)dr * row_step : C);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) v[r] += old[r];
+                    }
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int dr = i * 32 + 8 * (r >> 2) + (r & 3);
-                        const bool ok = colok && (full || row0 + dr < M);
-                        old[r] = *(ok ? pb + (int64_t)dr * row_step : C);
+                        if (colok && (full || row0 + dr < M)) pb[(int64_t)dr * row_step] = v[r];
                     }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) v[r] += old[r];
                 }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = i * 32 + 8 * (r >> 2) + (r & 3);
-                    if (colok && (full || row0 + dr < M)) pb[(int64_t)dr * row_step] = v[r];
-                }
-            }
+        }
+        }
+    };
+    for (int it = 0; it < my_tiles; ++it) {
+        const K2Tile tl = decode(it * G + perm);
+        using std::integral_constant;
+        typedef integral_constant<int, 0> c0;
+        typedef integral_constant<int, 1> c1;
+        typedef integral_constant<int, 2> c2;
+        typedef integral_constant<int, 3> c3;
+        typedef integral_constant<int, 4> c4;
+        if constexpr (!RAGGED) {
+            tile(tl, c2{}, c4{});
+            continue;
+        }
+        const int rows = k2_wave(tl, wave).rows;
+        if (rows == 2) {
+            if (tl.nu == 4) tile(tl, c2{}, c4{});
+            else if (tl.nu == 3) tile(tl, c2{}, c3{});
+            else if (tl.nu == 2) tile(tl, c2{}, c2{});
+            else tile(tl, c2{}, c1{});
+        } else if (rows == 1) {
+            if (tl.nu == 4) tile(tl, c1{}, c4{});
+            else if (tl.nu == 3) tile(tl, c1{}, c3{});
+            else if (tl.nu == 2) tile(tl, c1{}, c2{});
+            else tile(tl, c1{}, c1{});
+        } else {
+            tile(tl, c0{}, c1{});
+        }
     }
 }
 
@@ -669,50 +724,50 @@ int pace_launch(int grid, int total, int64_t K, hipStream_t s) {
 }
 }  // namespace
 
-hipError_t launch_contract_blocked_rowc(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
-                                        int batch, int accumulate, int cus, hipStream_t s) {
-    constexpr int BM = 256;
-    const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
-    const int total = tm * tn * batch;
+namespace {
+// One launch of the bf16 contraction (arguments as launch_contract's).
+template <bool BLOCKED, bool KMASK, bool CBLOCKED, bool TA = false, bool TB = false>
+hipError_t launch_ws(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                     int64_t ldc, int64_t sA, int64_t sB, int64_t sC, int batch, int accumulate, const uint8_t* kmask,
+                     int cus, hipStream_t s) {
+    if (CBLOCKED && !cblocked_fits(N, batch)) return hipErrorInvalidValue;
+    const K2Side sm = k2_side(TA ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, (int)M);
+    const K2Side sn = k2_side(TB ? kK2Transposed : BLOCKED ? kK2Blocked : kK2RowMajor, (int)N);
+    const int total = sm.tiles * sn.tiles * batch;
     const int grid = total < cus ? total : cus;
     const int pace = pace_launch(grid, total, K, s);
-    hipLaunchKernelGGL((k2_contract_ws<true, false, false>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A,
-                       (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, N, (int64_t)0, (int64_t)0, M * N, tm, tn,
-                       total, accumulate, (const uint8_t*)nullptr, pace);
+    const bool ragged = sm.units != 4 * sm.tiles || sn.units != 4 * sn.tiles;
+#define K2_WS(R_)                                                                                                  \
+    hipLaunchKernelGGL((k2_contract_ws<BLOCKED, KMASK, CBLOCKED, TA, TB, R_>), dim3(grid), dim3(768), 0, s,        \
+                       (const bf16_t*)A, (const bf16_t*)B, C, (int)M, (int)N, (int)K, (int)lda, (int)ldb, ldc, sA, \
+                       sB, sC, total, accumulate, kmask, pace)
+    if constexpr (BLOCKED) {   // row-major operands have whole tiles only
+        if (ragged) K2_WS(true);
+        else K2_WS(false);
+    } else {
+        K2_WS(false);
+    }
+#undef K2_WS
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_contract_blocked_rowc(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
+                                        int batch, int accumulate, int cus, hipStream_t s) {
+    return launch_ws<true, false, false>(A, B, C, M, N, K, 0, 0, N, 0, 0, M * N, batch, accumulate, nullptr, cus, s);
 }
 
 hipError_t launch_contract_blocked_packed(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
                                           int batch, int accumulate, int cus, hipStream_t s) {
-    constexpr int BM = 256;
-    const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
-    const int total = tm * tn * batch;
-    const int grid = total < cus ? total : cus;
-    if (!cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, K, s);
-    hipLaunchKernelGGL((k2_contract_ws<true, false, true>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A,
-                       (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, (int64_t)0, (int64_t)0, (int64_t)0,
-                       (int64_t)0, tm, tn, total, accumulate, (const uint8_t*)nullptr, pace);
-    return hipGetLastError();
+    return launch_ws<true, false, true>(A, B, C, M, N, K, 0, 0, 0, 0, 0, 0, batch, accumulate, nullptr, cus, s);
 }
 
 hipError_t launch_contract_transposed(int ta, int tb, const void* A, const void* B, float* C, int64_t M, int64_t N,
                                       int64_t K, int batch, int cus, hipStream_t s, int accumulate) {
-    constexpr int BM = 256;
-    const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
-    const int total = tm * tn * batch;
-    const int grid = total < cus ? total : cus;
-    if ((!ta && !tb) || !cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, K, s);
-#define K2_TR(TA_, TB_)                                                                                             \
-    hipLaunchKernelGGL((k2_contract_ws<true, false, true, TA_, TB_>), dim3(grid), dim3(768), 0, s, (const bf16_t*)A, \
-                       (const bf16_t*)B, C, (int)M, (int)N, (int)K, 0, 0, (int64_t)0, (int64_t)0, (int64_t)0,     \
-                       (int64_t)0, tm, tn, total, accumulate, (const uint8_t*)nullptr, pace)
-    if (!ta && tb) K2_TR(false, true);
-    else if (ta && tb) K2_TR(true, true);
-    else K2_TR(true, false);
-#undef K2_TR
-    return hipGetLastError();
+    if (!ta && !tb) return hipErrorInvalidValue;
+    if (!ta) return launch_ws<true, false, true, false, true>(A, B, C, M, N, K, 0, 0, 0, 0, 0, 0, batch, accumulate, nullptr, cus, s);
+    if (tb) return launch_ws<true, false, true, true, true>(A, B, C, M, N, K, 0, 0, 0, 0, 0, 0, batch, accumulate, nullptr, cus, s);
+    return launch_ws<true, false, true, true, false>(A, B, C, M, N, K, 0, 0, 0, 0, 0, 0, batch, accumulate, nullptr, cus, s);
 }
 
 hipError_t launch_stage_kmask(const uint8_t* mask, int64_t klen, uint8_t* dst, hipStream_t s) {
@@ -746,26 +801,12 @@ hipError_t launch_contract(int dtype, int blocked, const void* A, const void* B,
 #undef K2_F32
         return hipGetLastError();
     }
-    constexpr int BM = 256;
-    const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
-    const int total = tm * tn * batch;
-    const int grid = total < cus ? total : cus;
-    const bf16_t* a = (const bf16_t*)A;
-    const bf16_t* b = (const bf16_t*)B;
-    if (blocked && !cblocked_fits(N, batch)) return hipErrorInvalidValue;
-    const int pace = pace_launch(grid, total, K, s);
-#define K2_WS(BL, KM)                                                                                              \
-    hipLaunchKernelGGL((k2_contract_ws<BL, KM, BL>), dim3(grid), dim3(768), 0, s, a, b, C, (int)M, (int)N, (int)K, \
-                       (int)lda, (int)ldb, ldc, sA, sB, sC, tm, tn, total, accumulate, kmask, pace)
-    if (kmask) {
-        if (blocked) K2_WS(true, true);
-        else K2_WS(false, true);
-    } else {
-        if (blocked) K2_WS(true, false);
-        else K2_WS(false, false);
+    if (blocked) {   // the k-mask of a blocked operand was applied when it was written
+        if (kmask) return hipErrorInvalidValue;
+        return launch_ws<true, false, true>(A, B, C, M, N, K, 0, 0, 0, 0, 0, 0, batch, accumulate, nullptr, cus, s);
     }
-#undef K2_WS
-    return hipGetLastError();
+    if (kmask) return launch_ws<false, true, false>(A, B, C, M, N, K, lda, ldb, ldc, sA, sB, sC, batch, accumulate, kmask, cus, s);
+    return launch_ws<false, false, false>(A, B, C, M, N, K, lda, ldb, ldc, sA, sB, sC, batch, accumulate, nullptr, cus, s);
 }
 
 // Host-side walk over the direct-to-LDS loads of one k2_contract_ws launch,
@@ -790,16 +831,17 @@ int64_t k2_layout_off(const K2Operand& op, int ch, int64_t row, int64_t k) {
 
 void k2_check_operand(const K2Operand& op, uint64_t bytes, int ch, K2CheckCounts& n) {
     const int nk = (op.K + kK2BK - 1) / kK2BK;
-    const int tiles = (op.rows + kK2Tile - 1) / kK2Tile;
-    for (int tt = 0; tt < tiles; ++tt) {
-        const int t0 = tt * kK2Tile;
+    const K2Side side = k2_side(op.mode, op.rows);
+    for (int tt = 0; tt < side.tiles; ++tt) {
+        int t0, units;
+        k2_span(side, tt, t0, units);
         for (int kt = 0; kt < nk; ++kt) {
             const K2Desc d = k2_desc(op, ch, t0, kt);
             const bool desc_ok = d.base >= 0 && (d.range % 16) == 0 && (uint64_t)d.base * 2 + d.range <= bytes;
             for (int lw = 0; lw < kK2Loaders; ++lw)
                 for (int jj = 0; jj < kK2LoadsPerOperand; ++jj) {
                     uint32_t off = 0;
-                    const bool in = k2_load_off(op, t0, kt, lw, jj, off);
+                    const bool in = k2_load_off(op, t0, units, kt, lw, jj, off);
                     ++n.loads;
                     if (in && !desc_ok) ++n.bad_desc;
                     const uint32_t lds = k2_lds_off(lw, jj);
@@ -818,7 +860,7 @@ void k2_check_operand(const K2Operand& op, uint64_t bytes, int ch, K2CheckCounts
                                 row = t0 + r;
                                 k = (int64_t)kt * kK2BK + 8 * (slot ^ ((r >> 2) & 3)) + e;
                             }
-                            if (row >= op.rows || k >= op.K) continue;   // not needed by the tile
+                            if (row >= op.rows || row >= t0 + units * kK2Unit || k >= op.K) continue;   // not needed by the tile
                             ++n.elems;
                             const uint64_t byte = voff + 2u * (uint32_t)e;
                             const bool hit = in && byte + 2 <= d.range &&
@@ -832,24 +874,25 @@ void k2_check_operand(const K2Operand& op, uint64_t bytes, int ch, K2CheckCounts
 }
 }  // namespace
 
-void k2_check_c(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_channels, K2CheckCounts& n) {
-    n = K2CheckCounts{};
-    const int tm = (int)((M + kK2Tile - 1) / kK2Tile), tn = (int)((N + kK2Tile - 1) / kK2Tile);
+namespace {
+void k2_check_c_sides(const K2Side& sm, const K2Side& sn, int64_t M, int64_t N, int batch, uint64_t c_bytes,
+                      int all_channels, K2CheckCounts& n) {
     const int J = (int)((N + kResJ - 1) / kResJ);
     const uint32_t crs = k2_c_row_floats((int)N, batch);
-    n.tiles = (int64_t)tm * tn * batch;
+    n.tiles = (int64_t)sm.tiles * sn.tiles * batch;
     for (int ch = 0; ch < batch; ++ch) {
         if (!all_channels && ch != 0 && ch != batch - 1) continue;
         std::vector<uint8_t> hit((size_t)M * (size_t)N, 0);
-        for (int ti = 0; ti < tm; ++ti)
-            for (int tj = 0; tj < tn; ++tj) {
-                const K2Tile t{ch, ti * kK2Tile, tj * kK2Tile};
-                for (int wave = 0; wave < 8; ++wave)
-                    for (int j = 0; j < 4; ++j) {
-                        const K2Desc d = k2_c_desc((int)M, (int)N, batch, t, wave, j);
+        for (int ti = 0; ti < sm.tiles; ++ti)
+            for (int tj = 0; tj < sn.tiles; ++tj) {
+                const K2Tile t = k2_tile(sm, sn, ch, ti, tj);
+                for (int wave = 0; wave < 8; ++wave) {
+                    const K2Wave w = k2_wave(t, wave);
+                    for (int j = 0; j < w.cols; ++j) {
+                        const K2Desc d = k2_c_desc((int)M, (int)N, batch, t, w, j);
                         if (d.range && (d.base < 0 || (uint64_t)d.base * 4 + d.range > c_bytes)) ++n.bad_desc;
-                        for (int xr = 0; xr < 2; ++xr) {
-                            const int x = 4 * xr + j;
+                        for (int i = 0; i < w.rows; ++i) {
+                            const int x = 4 * i + j;
                             ++n.loads;
                             for (int r = 0; r < 16; ++r)
                                 for (int lane = 0; lane < 64; ++lane) {
@@ -874,35 +917,63 @@ void k2_check_c(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_chann
                                 }
                         }
                     }
+                }
             }
         for (uint8_t h : hit) n.bad_elem += h ? 0 : 1;
     }
+}
+}  // namespace
+
+void k2_check_c(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_channels, K2CheckCounts& n) {
+    n = K2CheckCounts{};
+    // the tile sides of blocked operands, then those of transposed and
+    // row-major ones where they differ
+    k2_check_c_sides(k2_side(kK2Blocked, (int)M), k2_side(kK2Blocked, (int)N), M, N, batch, c_bytes, all_channels, n);
+    const K2Side em = k2_side(kK2Transposed, (int)M), en = k2_side(kK2Transposed, (int)N);
+    if (em.units % 4 == 0 && en.units % 4 == 0) return;
+    K2CheckCounts e;
+    k2_check_c_sides(em, en, M, N, batch, c_bytes, all_channels, e);
+    if (e.elems != n.elems) ++n.bad_elem;
+    n.bad_desc += e.bad_desc;
+    n.bad_elem += e.bad_elem;
 }
 
 void k2_check_loads(int a_mode, int b_mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t sA,
                     int64_t sB, int batch, uint64_t a_bytes, uint64_t b_bytes, int grid, int all_channels,
                     K2CheckCounts& n) {
     n = K2CheckCounts{};
-    const int tm = (int)((M + kK2Tile - 1) / kK2Tile), tn = (int)((N + kK2Tile - 1) / kK2Tile);
-    const int64_t total = (int64_t)tm * tn * batch;
+    const K2Side sm = k2_side(a_mode, (int)M), sn = k2_side(b_mode, (int)N);
+    const int64_t total = (int64_t)sm.tiles * sn.tiles * batch;
     std::vector<uint8_t> seen((size_t)total, 0);
     for (int wg = 0; wg < grid; ++wg) {
         const int perm = k2_perm(wg, grid), mine = k2_my_tiles(perm, grid, (int)total);
         for (int it = 0; it < mine; ++it) {
-            const K2Tile t = k2_decode(it * grid + perm, tm, tn);
-            const bool ok = t.ch >= 0 && t.ch < batch && t.m0 >= 0 && t.m0 < M && t.n0 >= 0 && t.n0 < N &&
-                            t.m0 % kK2Tile == 0 && t.n0 % kK2Tile == 0;
+            int ch, ti, tj;
+            k2_index(sm, sn, it * grid + perm, ch, ti, tj);
+            const K2Tile t = k2_tile(sm, sn, ch, ti, tj);
+            const bool ok = ch >= 0 && ch < batch && ti >= 0 && ti < sm.tiles && tj >= 0 && tj < sn.tiles && t.m0 < M &&
+                            t.n0 < N && t.mu >= 1 && t.mu <= 4 && t.nu >= 1 && t.nu <= 4;
             if (!ok) {
                 ++n.bad_tiles;
                 continue;
             }
-            uint8_t& v = seen[((size_t)t.ch * tm + t.m0 / kK2Tile) * tn + t.n0 / kK2Tile];
+            uint8_t& v = seen[((size_t)ch * sm.tiles + ti) * sn.tiles + tj];
             if (v) ++n.bad_tiles;
             v = 1;
         }
     }
     for (uint8_t v : seen) n.bad_tiles += v ? 0 : 1;
     n.tiles = total;
+    for (const K2Side* s : {&sm, &sn}) {   // the spans follow each other and cover the side
+        int next = 0;
+        for (int i = 0; i < s->tiles; ++i) {
+            int t0, units;
+            k2_span(*s, i, t0, units);
+            if (t0 != next) ++n.bad_tiles;
+            next = t0 + units * kK2Unit;
+        }
+        if (next != s->units * kK2Unit) ++n.bad_tiles;
+    }
     const K2Operand opa{a_mode, (int)M, (int)K, (int)lda, sA}, opb{b_mode, (int)N, (int)K, (int)ldb, sB};
     for (int ch = 0; ch < batch; ++ch) {
         if (!all_channels && ch != 0 && ch != batch - 1) continue;

@@ -62,22 +62,78 @@ __host__ __device__ __forceinline__ int k2_perm(int wg, int G) {
 __host__ __device__ __forceinline__ int k2_my_tiles(int perm, int G, int total) {
     return perm < total ? (total - 1 - perm) / G + 1 : 0;
 }
-struct K2Tile {
-    int ch, m0, n0;
+//
+// Tile sides.  A side of `rows` rows is ceil(rows / 64) units of 64 rows over
+// ceil(rows / 256) tiles of one to four units; the matrix-core waves skip the
+// units a tile does not have, so a ragged size is padded to 64 and not to 256
+// (N = 300: 320^2 against 512^2).  The units are spread evenly over the tiles
+// (1300 rows: 4 4 4 3 3 3, not 4 4 4 4 4 1, whose narrow tile would pay the
+// loads and barriers of a wide one); a plain blocked operand keeps the
+// 256-row grid of its panel blocks, only its last tile is short.  Row-major
+// operands (panels too long for the padding to matter) always get whole tiles.
+constexpr int kK2Unit = 64;
+struct K2Side {
+    int units, tiles, even;
 };
-__host__ __device__ __forceinline__ K2Tile k2_decode(int L, int tiles_m, int tiles_n) {
-    constexpr int GR = 4;
-    const int tiles = tiles_m * tiles_n;
+__host__ __device__ __forceinline__ K2Side k2_side(int mode, int rows) {
+    const int tiles = (rows + kK2Tile - 1) / kK2Tile;
+    if (mode == kK2RowMajor) return K2Side{tiles * (kK2Tile / kK2Unit), tiles, 0};
+    return K2Side{(rows + kK2Unit - 1) / kK2Unit, tiles, mode == kK2Transposed};
+}
+struct K2Tile {
+    int ch, m0, n0;   // channel, first row of A and of B
+    int mu, nu;       // units of A and of B
+};
+__host__ __device__ __forceinline__ void k2_span(const K2Side& s, int i, int& t0, int& units) {
+    constexpr int kPer = kK2Tile / kK2Unit;
+    if (s.even) {
+        const int q = s.units / s.tiles, r = s.units - q * s.tiles;
+        t0 = (i * q + (i < r ? i : r)) * kK2Unit;
+        units = q + (i < r ? 1 : 0);
+    } else {
+        t0 = i * kK2Tile;
+        units = s.units - i * kPer < kPer ? s.units - i * kPer : kPer;
+    }
+}
+__host__ __device__ __forceinline__ K2Tile k2_tile(const K2Side& sm, const K2Side& sn, int ch, int ti, int tj) {
     K2Tile t;
-    t.ch = L / tiles;
-    const int rem = L - t.ch * tiles;
-    const int gid = rem / (GR * tiles_n);
-    const int first_m = gid * GR;
-    const int gsz = tiles_m - first_m < GR ? tiles_m - first_m : GR;
-    const int in_g = rem - gid * GR * tiles_n;
-    t.m0 = (first_m + in_g % gsz) * kK2Tile;
-    t.n0 = (in_g / gsz) * kK2Tile;
+    t.ch = ch;
+    k2_span(sm, ti, t.m0, t.mu);
+    k2_span(sn, tj, t.n0, t.nu);
     return t;
+}
+__host__ __device__ __forceinline__ void k2_index(const K2Side& sm, const K2Side& sn, int L, int& ch, int& ti, int& tj) {
+    constexpr int GR = 4;
+    const int tiles = sm.tiles * sn.tiles;
+    ch = L / tiles;
+    const int rem = L - ch * tiles;
+    const int gid = rem / (GR * sn.tiles);
+    const int first_m = gid * GR;
+    const int gsz = sm.tiles - first_m < GR ? sm.tiles - first_m : GR;
+    const int in_g = rem - gid * GR * sn.tiles;
+    ti = first_m + in_g % gsz;
+    tj = in_g / gsz;
+}
+__host__ __device__ __forceinline__ K2Tile k2_decode(const K2Side& sm, const K2Side& sn, int L) {
+    int ch, ti, tj;
+    k2_index(sm, sn, L, ch, ti, tj);
+    return k2_tile(sm, sn, ch, ti, tj);
+}
+// The 32-row blocks of a tile that MFMA wave w (0..7) owns: `rows` blocks of A
+// from block rb, `cols` blocks of B from block cb.  Waves w and w + 4 share a
+// SIMD, i.e. row pairs w / 2 and w / 2 + 2: the split gives every SIMD the
+// same work for any number of units (three units: 2 2 1 1 blocks).
+struct K2Wave {
+    int rb, rows, cb, cols;
+};
+__host__ __device__ __forceinline__ K2Wave k2_wave(const K2Tile& t, int wave) {
+    const int wm = wave >> 1, wn = wave & 1;
+    K2Wave w;
+    w.rows = t.mu == 4 ? 2 : t.mu == 3 ? (wm < 2 ? 2 : 1) : t.mu == 2 ? 1 : (wm < 2 ? 1 : 0);
+    w.rb = t.mu == 4 ? 2 * wm : t.mu == 3 ? (wm < 2 ? 2 * wm : 2 + wm) : wm;
+    w.cols = t.nu;
+    w.cb = wn * t.nu;
+    return w;
 }
 
 // ------------------------------------------------------------- loads
@@ -131,22 +187,23 @@ __host__ __device__ __forceinline__ K2Desc k2_desc(const K2Operand& op, int ch, 
 }
 
 // Wave-uniform byte offset of load jj of loader wave lw in step kt (added to
-// k2_lane_off).  Returns false when the whole load lies outside the operand
-// (a transposed operand's column block past its last one): the load then
-// goes to the empty descriptor.
-__host__ __device__ __forceinline__ bool k2_load_off(const K2Operand& op, int t0, int kt, int lw, int jj,
+// k2_lane_off).  Returns false when the tile does not have the loader wave's
+// unit of rows, or the whole load lies outside the operand (a transposed
+// operand's column block past its last one): the load then goes to the empty
+// descriptor.
+__host__ __device__ __forceinline__ bool k2_load_off(const K2Operand& op, int t0, int units, int kt, int lw, int jj,
                                                       uint32_t& off) {
     if (op.mode == kK2Transposed) {
         const int cb = (t0 >> 5) + 2 * lw + (jj >> 1);
         off = (uint32_t)cb * (uint32_t)(kK2Tile * kK2BK * 2) + (uint32_t)((kt & 7) * 32 + 16 * (jj & 1)) * kK2Row;
-        return cb < k2_tr_blocks(op);
+        return lw < units && cb < k2_tr_blocks(op);
     }
     if (op.mode == kK2Blocked) {
         off = (uint32_t)(jj * 16 * kK2BK * 2) + (uint32_t)kt * (uint32_t)(kK2Tile * kK2BK * 2);
     } else {
         off = (uint32_t)jj * (uint32_t)(16 * op.ld * 2) + (uint32_t)kt * kK2Row;
     }
-    return true;
+    return lw < units;
 }
 
 // LDS byte offset (within the operand's half of a stage) of load jj of
@@ -160,11 +217,10 @@ __host__ __device__ __forceinline__ uint32_t k2_lds_off(int lw, int jj) {
 // The result C of nch channels in the pair-blocked layout (result_off):
 // element (ch, i, j) at ((i * J + j / 32) * nch + ch) * 32 + j % 32 floats,
 // J = ceil(N / 32); a row is crs = J * nch * 32 floats long.  MFMA wave w
-// (0..7) of a tile owns its rows 64 (w / 2) .. + 63 and columns
-// 128 (w % 2) .. + 127, as eight 32 x 32 blocks x = 4 (rows / 32) + column
-// block; in the accumulator layout lane l holds column l % 32 and, in
-// register r, row 8 (r / 4) + 4 (l / 32) + r % 4 of a block.  Each of the
-// wave's four column blocks goes through one descriptor from the block's
+// (0..7) of a tile owns its blocks k2_wave, up to eight 32 x 32 blocks x =
+// 4 (row block) + column block; in the accumulator layout lane l holds column
+// l % 32 and, in register r, row 8 (r / 4) + 4 (l / 32) + r % 4 of a block.
+// Each of the wave's column blocks goes through one descriptor from the block's
 // first element whose range covers the rows < M, so that rows past M fall
 // outside it; a column block past C's last gets the empty descriptor (its
 // memory belongs to the next row).  Columns past N inside C's last block
@@ -174,11 +230,11 @@ __host__ __device__ __forceinline__ uint32_t k2_lds_off(int lw, int jj) {
 __host__ __device__ __forceinline__ uint32_t k2_c_row_floats(int N, int nch) {
     return (uint32_t)((N + kResJ - 1) / kResJ) * (uint32_t)nch * kResJ;
 }
-__host__ __device__ __forceinline__ K2Desc k2_c_desc(int M, int N, int nch, const K2Tile& t, int wave, int j) {
+__host__ __device__ __forceinline__ K2Desc k2_c_desc(int M, int N, int nch, const K2Tile& t, const K2Wave& w, int j) {
     const int jblocks = (N + kResJ - 1) / kResJ;
-    const int wrow0 = t.m0 + (wave >> 1) * 64, wcol0 = t.n0 + (wave & 1) * 128;
-    const int nrows = M - wrow0 < 64 ? M - wrow0 : 64;
-    const bool live = nrows > 0 && wcol0 / kResJ + j < jblocks;
+    const int wrow0 = t.m0 + 32 * w.rb, wcol0 = t.n0 + 32 * w.cb;
+    const int nrows = M - wrow0 < 32 * w.rows ? M - wrow0 : 32 * w.rows;
+    const bool live = nrows > 0 && j < w.cols && wcol0 / kResJ + j < jblocks;
     K2Desc d;
     d.base = live ? result_off(jblocks, nch, t.ch, wrow0, wcol0 + kResJ * j) : 0;
     d.range = live ? ((uint32_t)(nrows - 1) * k2_c_row_floats(N, nch) + kResJ) * 4u : 0u;
@@ -192,8 +248,9 @@ __host__ __device__ __forceinline__ uint32_t k2_c_reg_off(uint32_t crs, int x, i
 }
 // The logical row and column of that element (for the host check).
 __host__ __device__ __forceinline__ void k2_c_elem(const K2Tile& t, int wave, int lane, int x, int r, int& row, int& col) {
-    row = t.m0 + (wave >> 1) * 64 + (x >> 2) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    col = t.n0 + (wave & 1) * 128 + (x & 3) * 32 + (lane & 31);
+    const K2Wave w = k2_wave(t, wave);
+    row = t.m0 + (w.rb + (x >> 2)) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    col = t.n0 + (w.cb + (x & 3)) * 32 + (lane & 31);
 }
 
 }  // namespace trimul
