@@ -976,6 +976,9 @@ constexpr int64_t kOpmMaxSeq = 65536;    // sequences per step
 size_t opm_panel_bytes(int64_t rows, int64_t K) {
     return round256((size_t)trimul::panel_elems(trimul::panel_geom(rows, K)) * 2);
 }
+
+// Bytes of the mask words of `tokens` tokens and slen sequences (to the panel's 256-row boundary).
+size_t opm_bits_bytes(int64_t slen, int64_t tokens) { return round256((size_t)((slen + 255) / 256 * 8) * (size_t)tokens * 4); }
 size_t opm_sum_bytes(int64_t rows, int64_t cols) { return round256((size_t)rows * 32 * (size_t)cols * 32 * 4); }
 size_t opm_cnt_bytes(int64_t rows, int64_t cols) { return round256((size_t)rows * (size_t)((cols + 31) / 32 * 32) * 4); }
 
@@ -1063,9 +1066,9 @@ int opm_workspace_size(opm_handle_t h, int64_t rows, int64_t cols, int64_t slen,
     if (rows < 1 || cols < 1 || rows > kOpmMaxTile || cols > kOpmMaxTile)
         return fail(TRI_MUL_EINVAL, "tile %lld x %lld outside [1, %lld]^2", (long long)rows, (long long)cols, (long long)kOpmMaxTile);
     if (slen < 1 || slen > kOpmMaxSeq) return fail(TRI_MUL_EINVAL, "slen = %lld outside [1, %lld]", (long long)slen, (long long)kOpmMaxSeq);
-    // the sums' operands transposed (slen rows, tokens * 32 columns), the counts' plain
-    *bytes = opm_panel_bytes(slen, rows * 32) + opm_panel_bytes(slen, cols * 32) + opm_panel_bytes(rows, slen) +
-             opm_panel_bytes(cols, slen);
+    // the sums' operands transposed (slen rows, tokens * 32 columns), the counts' mask words
+    *bytes = opm_panel_bytes(slen, rows * 32) + opm_panel_bytes(slen, cols * 32) + opm_bits_bytes(slen, rows) +
+             opm_bits_bytes(slen, cols);
     return ok();
 }
 
@@ -1091,22 +1094,21 @@ int opm_block_accumulate(opm_handle_t h, const opm_block_view_t* v, const void* 
     p += opm_panel_bytes(v->slen, v->rows * 32);
     void* PB = p;
     p += opm_panel_bytes(v->slen, v->cols * 32);
-    void* MA = p;
-    p += opm_panel_bytes(v->rows, v->slen);
-    void* MB = p;
+    uint32_t* MA = reinterpret_cast<uint32_t*>(p);
+    p += opm_bits_bytes(v->slen, v->rows);
+    uint32_t* MB = reinterpret_cast<uint32_t*>(p);
     float* sums = acc;
     float* cnt = reinterpret_cast<float*>(reinterpret_cast<char*>(acc) + opm_sum_bytes(v->rows, v->cols));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = trimul::launch_opm_pack(a, mask, v->n_total, v->row0, v->rows, v->s0, v->slen, PA, MA, s);
-    if (e == hipSuccess) e = trimul::launch_opm_pack(b, mask, v->n_total, v->col0, v->cols, v->s0, v->slen, PB, MB, s);
+    hipError_t e = trimul::launch_opm_pack(a, b, mask, v->n_total, v->row0, v->rows, v->col0, v->cols, v->s0, v->slen, PA, PB,
+                                           MA, MB, s);
     if (e != hipSuccess) return hip_fail(e, "pack kernel launch");
     const int accumulate = v->k_index > 0;
     e = trimul::launch_contract_transposed(1, 1, PA, PB, sums, v->rows * 32, v->cols * 32, v->slen, 1, h->cus, s,
                                            accumulate);
     if (e == hipSuccess)
-        e = trimul::launch_contract(TRI_MUL_BF16, 1, MA, MB, cnt, v->rows, v->cols, v->slen, 0, 0, 0, 0, 0, 0, 1,
-                                    accumulate, nullptr, h->cus, s);
-    if (e != hipSuccess) return hip_fail(e, "contraction kernel launch");
+        e = trimul::launch_opm_count(MA, MB, v->rows, v->cols, v->slen, accumulate, cnt, s);
+    if (e != hipSuccess) return hip_fail(e, "contraction or count kernel launch");
     if (last) {
         e = trimul::launch_opm_epilogue(h->out_dtype == TRI_MUL_BF16, sums, cnt, v->rows, v->cols, h->wo, h->bo,
                                         out_tile, h->cus, s);

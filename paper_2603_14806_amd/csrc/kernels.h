@@ -158,15 +158,19 @@ struct SumTasks {
 };
 hipError_t launch_sum_parts(const SumTask* tasks, int count, hipStream_t s);
 
-// Outer product mean (opm.hip).  Pack: tokens [tok0, tok0 + ntok) and
-// sequences [s0, s0 + slen) of a [S][n_total][32] bf16 tensor, masked, into
-// the transposed operand of the sums -- the blocked panel of slen rows and
-// ntok * 32 columns, X[s][token * 32 + c] -- and the 0/1 mask into the
-// (plain) blocked panel of ntok rows and K = slen.  Epilogue: out[rows][cols][128]
-// from the sums O (result layout, [rows * 32][cols * 32]) and the counts
-// (result layout, [rows][32 * ceil(cols / 32)]).
-hipError_t launch_opm_pack(const void* a, const uint8_t* mask, int64_t n_total, int64_t tok0, int64_t ntok,
-                           int64_t s0, int64_t slen, void* P, void* Mp, hipStream_t s);
+// Outer product mean (opm.hip).  Pack: tokens [row0, row0 + rows) of a and
+// [col0, col0 + cols) of b, sequences [s0, s0 + slen) of [S][n_total][32] bf16
+// tensors, masked, into the transposed operands of the sums -- the blocked
+// panels of slen rows and tokens * 32 columns, X[s][token * 32 + c] -- and the
+// mask into words of 32 sequences, bits[s / 32][token] (8 * ceil(slen / 256)
+// words per token).  Count: the pairs' common sequences from those words into
+// [rows][32 * ceil(cols / 32)] floats.  Epilogue: out[rows][cols][128] from the
+// sums O (result layout, [rows * 32][cols * 32]) and the counts.
+hipError_t launch_opm_pack(const void* a, const void* b, const uint8_t* mask, int64_t n_total, int64_t row0,
+                           int64_t rows, int64_t col0, int64_t cols, int64_t s0, int64_t slen, void* PA, void* PB,
+                           uint32_t* abits, uint32_t* bbits, hipStream_t s);
+hipError_t launch_opm_count(const uint32_t* abits, const uint32_t* bbits, int64_t rows, int64_t cols, int64_t slen,
+                            int accumulate, float* cnt, hipStream_t s);
 hipError_t launch_opm_epilogue(int out_dtype, const float* O, const float* cnt, int64_t rows, int64_t cols,
                                const uint16_t* wo, const float* bo, void* out, int cus, hipStream_t s);
 

@@ -25,39 +25,104 @@ constexpr int kOz = 128;       // output channels
 // where the 32-column block of token tok and the 256-row block of sequences
 // s / 256 is one contiguous 16 KB block holding, for each sequence, the 64
 // bytes a[s][tok][0:32] as they are in the input.  So the pack is a masked
-// copy, no transpose.  One work-group per (8 tokens, 32 sequences): thread t
-// takes token part t % 8 (eight consecutive tokens of one sequence read 512
-// contiguous bytes) and sequence t / 8 (the eight sequences of a wave and
-// token write 512 contiguous bytes).  Sequences from slen up to the panel's
-// 256-row boundary get zeros; tokens past ntok have no columns and write
-// nothing.  The pair counts' operands keep the plain blocked layout (row =
-// token, k = s, bf16 0/1), written for k below the panel's 32-step boundary.
-__global__ __launch_bounds__(256) void k_opm_pack(const bf16_t* __restrict__ a, const uint8_t* __restrict__ mask,
-                                                  int64_t n_total, int64_t tok0, int ntok, int64_t s0, int slen,
-                                                  bf16_t* __restrict__ P, bf16_t* __restrict__ Mp) {
+// copy, no transpose.  One work-group per (8 tokens, 32 sequences) of a or of
+// b (grid z): a wave's loads take two sequences, 512 contiguous bytes of eight
+// tokens each, and its stores 128 bytes per token.  Sequences from slen up to
+// the panel's 256-row boundary get zeros; tokens past ntok have no columns and
+// write nothing.  The token mask of the work-group's 32 sequences goes to the
+// pair counts as one word per token, bit = sequence: bits[s / 32][ntok].
+// Bound by memory: 130 MB in and out per operand at S = 2048, N = 500, 2 x 48 us
+// as one launch per operand with 16-byte loads 64 bytes apart, now 46 for both.
+struct OpmPackArgs {
+    const bf16_t* a;
+    bf16_t* P;
+    uint32_t* bits;
+    int64_t tok0;
+    int ntok;
+};
+__global__ __launch_bounds__(256) void k_opm_pack(OpmPackArgs pa, OpmPackArgs pb, const uint8_t* __restrict__ mask,
+                                                  int64_t n_total, int64_t s0, int slen) {
+    __shared__ uint32_t keep[32][8];      // all ones where the token is present
+    __shared__ uint64_t present[4];       // wave w: bit 8 (s % 8) + token of sequences 8 w ..
+    const OpmPackArgs p = blockIdx.z ? pb : pa;
     const int t = threadIdx.x;
-    const int part = t & 7, sl = t >> 3;
-    const int tok = blockIdx.y * 8 + part, s = blockIdx.x * 32 + sl;
-    uint4 v[4] = {};
-    bf16_t m = 0;
-    if (tok < ntok && s < slen) {
-        const int64_t src = ((s0 + s) * n_total + tok0 + tok);
-        const uint8_t mk = mask ? mask[src] : (uint8_t)1;
-        if (mk) {
-            const uint4* p = reinterpret_cast<const uint4*>(a + src * kD);
+    const int t8 = blockIdx.y * 8, sg = blockIdx.x * 32;
+    if (t8 >= p.ntok) return;             // the other operand has more tokens
+    const int part = t & 3, tk = (t >> 2) & 7, s8 = t >> 5;
+    uint4 v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = p[q];
-            m = 0x3f80;   // bf16 1.0
+    for (int i = 0; i < 4; ++i) {
+        const int s = sg + s8 + 8 * i;
+        v[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (t8 + tk < p.ntok && s < slen)
+            v[i] = reinterpret_cast<const uint4*>(p.a + ((s0 + s) * n_total + p.tok0 + t8 + tk) * kD)[part];
+    }
+    {
+        const int s = sg + (t >> 3), tok = t8 + (t & 7);
+        const bool on = tok < p.ntok && s < slen && (!mask || mask[(s0 + s) * n_total + p.tok0 + tok] != 0);
+        keep[t >> 3][t & 7] = on ? 0xffffffffu : 0u;
+        const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+        if ((t & 63) == 0) present[t >> 6] = b;
+    }
+    __syncthreads();
+    if (t < 8 && t8 + t < p.ntok) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int q = 0; q < 32; ++q) word |= (uint32_t)((present[q >> 3] >> (8 * (q & 7) + t)) & 1u) << q;
+        p.bits[(int64_t)blockIdx.x * p.ntok + t8 + t] = word;
+    }
+    if (t8 + tk >= p.ntok) return;
+    const PanelGeom xg = panel_geom(slen, (int64_t)p.ntok * kD);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int s = s8 + 8 * i;
+        const uint32_t m = keep[s][tk];
+        reinterpret_cast<uint4*>(p.P + panel_off(xg, 0, sg + s, (int64_t)(t8 + tk) * kD))[part] =
+            make_uint4(v[i].x & m, v[i].y & m, v[i].z & m, v[i].w & m);
+    }
+}
+
+// Pair counts: cnt[i][j] (+)= sum_s m_si m_sj = the set bits two tokens share,
+// row-major with rows of 32 * ceil(cols / 32) floats (whole numbers, exact in
+// fp32 up to 2^24).  A work-group counts 32 x 32 pairs, a thread four, from 32
+// words per token and step in LDS.  As a product of 0/1 operands on the
+// contraction kernel this had ceil(N / 256)^2 work-groups, four at N = 500:
+// 48 us for S = 2048, now 11.
+__global__ __launch_bounds__(256) void k_opm_count(const uint32_t* __restrict__ abits, const uint32_t* __restrict__ bbits,
+                                                   int rows, int cols, int words, int accumulate,
+                                                   float* __restrict__ cnt) {
+    __shared__ uint32_t as[32][32];                            // [word][token]
+    __shared__ __align__(16) uint32_t bs[32][32];
+    const int t = threadIdx.x, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+    const int il = t >> 3, jl = 4 * (t & 7);
+    uint32_t n[4] = {0u, 0u, 0u, 0u};
+    for (int w0 = 0; w0 < words; w0 += 32) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int w = w0 + (t >> 5) + 8 * k, tk = t & 31;
+            as[(t >> 5) + 8 * k][tk] = w < words && i0 + tk < rows ? abits[(int64_t)w * rows + i0 + tk] : 0u;
+            bs[(t >> 5) + 8 * k][tk] = w < words && j0 + tk < cols ? bbits[(int64_t)w * cols + j0 + tk] : 0u;
+        }
+        __syncthreads();
+#pragma unroll 8
+        for (int w = 0; w < 32; ++w) {
+            const uint32_t x = as[w][il];
+            const uint4 y = *reinterpret_cast<const uint4*>(&bs[w][jl]);
+            n[0] += __popc(x & y.x);
+            n[1] += __popc(x & y.y);
+            n[2] += __popc(x & y.z);
+            n[3] += __popc(x & y.w);
         }
     }
-    if (tok < ntok) {
-        const PanelGeom xg = panel_geom(slen, (int64_t)ntok * kD);
-        uint4* dst = reinterpret_cast<uint4*>(P + panel_off(xg, 0, s, (int64_t)tok * kD));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) dst[q] = v[q];
-    }
-    const PanelGeom mg = panel_geom(ntok, slen);
-    if (s < mg.ksteps * 32) Mp[panel_off(mg, 0, tok, s)] = m;
+    if (i0 + il >= rows) return;
+    float4* dst = reinterpret_cast<float4*>(cnt + (int64_t)(i0 + il) * gridDim.x * 32 + j0 + jl);
+    float4 o = accumulate ? *dst : make_float4(0.f, 0.f, 0.f, 0.f);
+    o.x += (float)n[0];
+    o.y += (float)n[1];
+    o.z += (float)n[2];
+    o.w += (float)n[3];
+    *dst = o;
 }
 
 // ---------------------------------------------------------------- epilogue
@@ -200,11 +265,22 @@ __global__ __launch_bounds__(kEt) void k_opm_epilogue(const float* __restrict__ 
 
 }  // namespace
 
-hipError_t launch_opm_pack(const void* a, const uint8_t* mask, int64_t n_total, int64_t tok0, int64_t ntok,
-                           int64_t s0, int64_t slen, void* P, void* Mp, hipStream_t s) {
-    const dim3 grid((unsigned)((slen + 255) / 256 * 8), (unsigned)((ntok + 7) / 8));
-    hipLaunchKernelGGL(k_opm_pack, grid, dim3(256), 0, s, (const bf16_t*)a, mask, n_total, tok0, (int)ntok, s0,
-                       (int)slen, (bf16_t*)P, (bf16_t*)Mp);
+hipError_t launch_opm_pack(const void* a, const void* b, const uint8_t* mask, int64_t n_total, int64_t row0,
+                           int64_t rows, int64_t col0, int64_t cols, int64_t s0, int64_t slen, void* PA, void* PB,
+                           uint32_t* abits, uint32_t* bbits, hipStream_t s) {
+    const int64_t ntok = rows > cols ? rows : cols;
+    const dim3 grid((unsigned)((slen + 255) / 256 * 8), (unsigned)((ntok + 7) / 8), 2);
+    const OpmPackArgs pa{(const bf16_t*)a, (bf16_t*)PA, abits, row0, (int)rows};
+    const OpmPackArgs pb{(const bf16_t*)b, (bf16_t*)PB, bbits, col0, (int)cols};
+    hipLaunchKernelGGL(k_opm_pack, grid, dim3(256), 0, s, pa, pb, mask, n_total, s0, (int)slen);
+    return hipGetLastError();
+}
+
+hipError_t launch_opm_count(const uint32_t* abits, const uint32_t* bbits, int64_t rows, int64_t cols, int64_t slen,
+                            int accumulate, float* cnt, hipStream_t s) {
+    const dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32));
+    hipLaunchKernelGGL(k_opm_count, grid, dim3(256), 0, s, abits, bbits, (int)rows, (int)cols, (int)((slen + 31) / 32),
+                       accumulate, cnt);
     return hipGetLastError();
 }
 
