@@ -356,7 +356,12 @@ hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ld
                                int64_t k0, int64_t M, int64_t K, int incoming, void* A, void* B, hipStream_t s) {
     const int nch = (int)((K + kP1 - 1) / kP1);
     const int nlines = (int)(M * nch);
-    const unsigned g = (unsigned)(nlines < 2 * w.cus ? nlines : 2 * w.cus);
+    // Two work-groups per compute unit, but one up to four lines each: every
+    // work-group reads the 128 KB of weights, which is what a small call waits
+    // for (N = 100 12.0 -> 10.4 us, N = 130 15.4 -> 12.6, N = 160 15.6 -> 14.2;
+    // N = 200 18.6 against 19.0, N = 512 59 against 68).
+    const int cap = nlines <= 4 * w.cus ? w.cus : 2 * w.cus;
+    const unsigned g = (unsigned)(nlines < cap ? nlines : cap);
     const int64_t lo = std::min(m0, k0);   // the mask bytes read start here
     const uint32_t koff = (uint32_t)(k0 - lo), roff = (uint32_t)(m0 - lo);
     const uint8_t* mk = mask ? mask + lo : nullptr;
