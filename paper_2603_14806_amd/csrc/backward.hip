@@ -548,15 +548,13 @@ __global__ __launch_bounds__(kBT) void k_epilogue_backward(
 // Writes dz, unit blocks dpa, dga, dpb, dgb, x, and per-work-group sums of
 // dgamma_in, dbeta_in at partial[(2 wg + {0, 1}) * 128 + d].
 //
-// Wave w owns 32 output columns of both products and keeps both weight
-// slices in registers: rows 32 w + col of W_a, W_ga, W_b, W_gb for the
-// projections and row d = 32 w + col of [W_a^T | W_ga^T | W_b^T | W_gb^T]
-// (512 long) for dx, 256 registers; so the kernel runs 4 waves, one per
-// SIMD, each with the whole register file.  Products on
-// v_mfma_f32_32x32x16_bf16: lane l supplies row (column) l % 32 and k values
-// 8 (l / 32) .. + 7; the result gives lane l column l % 32 and rows
-// 8 (i / 4) + 4 (l / 32) + i % 4, i = 0 .. 15.
-constexpr int kPT = 256;      // threads of the projection backward
+// 8 waves, wave w owning the 16 output columns 16 w .. of every product, as in
+// the epilogue backward, with both weight slices in registers: rows 16 w + col
+// of W_a, W_ga, W_b, W_gb for the projections and row d = 16 w + col of
+// [W_a^T | W_ga^T | W_b^T | W_gb^T] (512 long) for dx, 128 registers.  (Four
+// waves of 32 columns read the gradients from LDS half as often, but fill the
+// register file with one wave per SIMD, whose every wait stood alone: N =
+// 1024 961 us, now 793; N = 384 166, now 144.)
 constexpr int kPq4 = 136;     // [pair][channel] row stride: rows 4 apart land 32 banks apart
 // Padded bf16 row tiles: a row of 128 (x) or 512 (the four gradients)
 // values plus one 16-byte chunk, so the 16 rows an operand read touches
@@ -578,8 +576,7 @@ __device__ __forceinline__ uint4 gather_col8p(const char* tile, int q0, int col)
 }
 
 template <bool INCOMING>
-__global__ __attribute__((amdgpu_flat_work_group_size(kPT, kPT), amdgpu_waves_per_eu(1, 1)))
-void k_projection_backward(
+__global__ __launch_bounds__(kBT) void k_projection_backward(
     const bf16_t* __restrict__ z, const uint8_t* __restrict__ mask, int N, int64_t units, const float* __restrict__ dA,
     const float* __restrict__ dB, const float* __restrict__ dxg, const bf16_t* __restrict__ wproj,
     const bf16_t* __restrict__ wprojt, const float* __restrict__ lniw, const float* __restrict__ lnib, float eps,
@@ -592,19 +589,18 @@ void k_projection_backward(
     __shared__ __align__(16) float dxs[kQ * kPq4];       // dx from the projections [q][d]
     __shared__ __align__(16) float xhs[kQ * kPq4];       // LN_in(z) normalised [q][d]
     __shared__ float rzs[kQ];                            // 1 / std of LN_in per pair
-    __shared__ float prm[2][128];                        // gamma_in, beta_in
+    __shared__ __align__(16) float prm[2][128];          // gamma_in, beta_in
     __shared__ float mq[kQ];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int lp = t >> 3, lq = t & 7;                   // LayerNorm: pair lp, d = 16 lq .. + 15
+    const int lp = t >> 4, lq = t & 15;                  // LayerNorm: pair lp, d = 8 lq .. + 7
     const int J = (N + kQ - 1) / kQ;
     auto pair_of = [&](int r, int k) -> int64_t { return INCOMING ? (int64_t)k * N + r : (int64_t)r * N + k; };
-
 
     // One unit's loads, issued one unit ahead; dx_g is fetched separately
     // (it is used last).  Nothing here reads the loaded registers.
     struct Pre {
-        float4 a[4], b[4];       // dA, dB block floats 4 (t + 256 s) ..
-        uint4 z0, z1;            // z of pair lp, channels 16 lq .. + 15
+        float4 a[2], b[2];       // dA, dB block floats 4 (t + 512 s) ..
+        uint4 z0;                // z of pair lp, channels 8 lq .. + 7
         uint32_t mr, mk;
     };
     // Byte distance between consecutive pairs of a unit in [pair][c_z]
@@ -619,43 +615,45 @@ void k_projection_backward(
         const auto ra = make_rsrc(dA + uu * (kCh * kQ), valid ? kCh * kQ * 4 : 0);
         const auto rb = make_rsrc(dB + uu * (kCh * kQ), valid ? kCh * kQ * 4 : 0);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            p.a[s] = bld_f4(ra, 16 * (t + kPT * s));
-            p.b[s] = bld_f4(rb, 16 * (t + kPT * s));
+        for (int s = 0; s < 2; ++s) {
+            p.a[s] = bld_f4(ra, 16 * (t + kBT * s));
+            p.b[s] = bld_f4(rb, 16 * (t + kBT * s));
         }
         const auto rzr = make_rsrc(z + pair_of(r, k0) * kCz, valid ? (np - 1) * step2 + kCz * 2 : 0);
-        p.z0 = buf_load16(rzr, lp * step2 + 32 * lq);
-        p.z1 = buf_load16(rzr, lp * step2 + 32 * lq + 16);
+        p.z0 = buf_load16(rzr, lp * step2 + 16 * lq);
         const auto rm = make_rsrc(mask, (valid && mask) ? (uint32_t)N : 0u);
         p.mr = bld_u8(rm, opaque(r));                    // per lane: a uniform load would be waited for at once
         p.mk = bld_u8(rm, k0 + (t & (kQ - 1)));
     };
-    auto load_dxg = [&](int64_t u, float4 (&g)[4]) {
+    auto load_dxg = [&](int64_t u, float4 (&g)[2]) {
         const bool valid = u < units;
         const int64_t uu = valid ? u : 0;
         const int r = (int)(uu / J), k0 = (int)(uu - (int64_t)r * J) * kQ;
         const int np = min(kQ, N - k0);
         const auto rg = make_rsrc(dxg + pair_of(r, k0) * kCz, valid ? (np - 1) * step4 + kCz * 4 : 0);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) g[s] = bld_f4(rg, lp * step4 + 64 * lq + 16 * s);
+        for (int s = 0; s < 2; ++s) g[s] = bld_f4(rg, lp * step4 + 32 * lq + 16 * s);
     };
 
-    float accg[16], accb[16];                            // dgamma_in, dbeta_in of d = 16 lq + i
+    float accg[8], accb[8];                              // dgamma_in, dbeta_in of d = 8 lq + i
 #pragma unroll
-    for (int i = 0; i < 16; ++i) accg[i] = accb[i] = 0.f;
+    for (int i = 0; i < 8; ++i) accg[i] = accb[i] = 0.f;
     Pre cur;
-    float4 xg[4];
+    float4 xg[2];
     load(blockIdx.x, cur);
     load_dxg(blockIdx.x, xg);
-    bf16x8_t wp[32], wt[32];   // wp[8 m + ks]: map m, k = 16 ks + 8 hi;  wt[ks]: k = 16 ks + 8 hi
+    bf16x8_t wp[4][4], wt[16];   // wp[m][ks]: map m, k = 32 ks + 8 kq;  wt[ks]: k = 32 ks + 8 kq
     {
-        const int col = lane & 31, hi = lane >> 5;
+        const int c = 16 * w + (lane & 15), kq = lane >> 4;
 #pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            wp[j] = *reinterpret_cast<const bf16x8_t*>(
-                wproj + ((int64_t)w * 128 + (j >> 3) * 32 + col) * 128 + 16 * (j & 7) + 8 * hi);
-            wt[j] = *reinterpret_cast<const bf16x8_t*>(wprojt + (int64_t)(32 * w + col) * 512 + 16 * j + 8 * hi);
-        }
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                wp[m][ks] = *reinterpret_cast<const bf16x8_t*>(
+                    wproj + ((int64_t)(c >> 5) * 128 + m * 32 + (c & 31)) * 128 + 32 * ks + 8 * kq);
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks)
+            wt[ks] = *reinterpret_cast<const bf16x8_t*>(wprojt + (int64_t)c * 512 + 32 * ks + 8 * kq);
     }
     if (t < 128) {
         prm[0][t] = lniw[t];
@@ -670,80 +668,87 @@ void k_projection_backward(
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
         const int r = (int)(u / J), k0 = (int)(u - (int64_t)r * J) * kQ;
         const int np = min(kQ, N - k0);
-        float xh[16], rz;   // LN_in(z) normalised, d = 16 lq + i, and 1 / std: to LDS after the barrier
+        float xh[8], rz;   // LN_in(z) normalised, d = 8 lq + i, and 1 / std: to LDS after the barrier
         {   // stage da, db and the mask; LN_in of pair lp -> x hi / lo rows
-            const int t = opaque(threadIdx.x), lp = t >> 3, lq = t & 7;
+            const int t = opaque(threadIdx.x), lp = t >> 4, lq = t & 15;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int c = (t >> 3) + 32 * s, q = 4 * (t & 7);
+            for (int s = 0; s < 2; ++s) {
+                const int c = (t >> 3) + 64 * s, q = 4 * (t & 7);
                 *reinterpret_cast<float4*>(&das[c * kCs + q]) = cur.a[s];
                 *reinterpret_cast<float4*>(&dbs[c * kCs + q]) = cur.b[s];
             }
             if (t < kQ) mq[t] = (t < np && (!mask || (cur.mr != 0 && cur.mk != 0))) ? 1.f : 0.f;
-            const uint32_t zw[8] = {cur.z0.x, cur.z0.y, cur.z0.z, cur.z0.w, cur.z1.x, cur.z1.y, cur.z1.z, cur.z1.w};
+            const uint32_t zw[4] = {cur.z0.x, cur.z0.y, cur.z0.z, cur.z0.w};
             float s1 = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < 4; ++i) {
                 xh[2 * i] = __uint_as_float(zw[i] << 16);
                 xh[2 * i + 1] = __uint_as_float(zw[i] & 0xffff0000u);
             }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s1 += xh[i];
-            const float mz = sum_lanes8(s1) * (1.f / kCz);
+            for (int i = 0; i < 8; ++i) s1 += xh[i];
+            const float mz = sum_lanes16(s1) * (1.f / kCz);
             float q2 = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { xh[i] -= mz; q2 += xh[i] * xh[i]; }
-            rz = rsqrtf(sum_lanes8(q2) * (1.f / kCz) + eps);
-            uint32_t hw[8], lw[8];
+            for (int i = 0; i < 8; ++i) { xh[i] -= mz; q2 += xh[i] * xh[i]; }
+            rz = rsqrtf(sum_lanes16(q2) * (1.f / kCz) + eps);
+            float gam[8], bet[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int d = 16 * lq + 2 * i;
+            for (int s = 0; s < 2; ++s) {
+                const float4 g = *reinterpret_cast<const float4*>(&prm[0][8 * lq + 4 * s]);
+                const float4 b = *reinterpret_cast<const float4*>(&prm[1][8 * lq + 4 * s]);
+                gam[4 * s] = g.x; gam[4 * s + 1] = g.y; gam[4 * s + 2] = g.z; gam[4 * s + 3] = g.w;
+                bet[4 * s] = b.x; bet[4 * s + 1] = b.y; bet[4 * s + 2] = b.z; bet[4 * s + 3] = b.w;
+            }
+            uint32_t hw[4], lw[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
                 xh[2 * i] *= rz;
                 xh[2 * i + 1] *= rz;
-                const float x0 = xh[2 * i] * prm[0][d] + prm[1][d];
-                const float x1 = xh[2 * i + 1] * prm[0][d + 1] + prm[1][d + 1];
+                const float x0 = xh[2 * i] * gam[2 * i] + bet[2 * i];
+                const float x1 = xh[2 * i + 1] * gam[2 * i + 1] + bet[2 * i + 1];
                 hw[i] = pack_bf16x2(x0, x1);
                 lw[i] = pack_bf16x2(x0 - __uint_as_float(hw[i] << 16), x1 - __uint_as_float(hw[i] & 0xffff0000u));
             }
-            *reinterpret_cast<uint4*>(xa[0] + lp * kXrow + 32 * lq) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-            *reinterpret_cast<uint4*>(xa[0] + lp * kXrow + 32 * lq + 16) = make_uint4(hw[4], hw[5], hw[6], hw[7]);
-            *reinterpret_cast<uint4*>(xa[1] + lp * kXrow + 32 * lq) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-            *reinterpret_cast<uint4*>(xa[1] + lp * kXrow + 32 * lq + 16) = make_uint4(lw[4], lw[5], lw[6], lw[7]);
+            *reinterpret_cast<uint4*>(xa[0] + lp * kXrow + 16 * lq) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            *reinterpret_cast<uint4*>(xa[1] + lp * kXrow + 16 * lq) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
         }
         load(u + gridDim.x, cur);                        // next unit's dA, dB, z, mask
         __syncthreads();
         {   // xhs and rzs are read by the previous unit's last phase: written only past the barrier
-            const int t = opaque(threadIdx.x), lp = t >> 3, lq = t & 7;
+            const int t = opaque(threadIdx.x), lp = t >> 4, lq = t & 15;
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                *reinterpret_cast<float4*>(&xhs[lp * kPq4 + 16 * lq + 4 * s]) =
+            for (int s = 0; s < 2; ++s)
+                *reinterpret_cast<float4*>(&xhs[lp * kPq4 + 8 * lq + 4 * s]) =
                     make_float4(xh[4 * s], xh[4 * s + 1], xh[4 * s + 2], xh[4 * s + 3]);
             if (lq == 0) rzs[lp] = rz;
         }
-        {   // projections of channels c = 32 w + col; the four gradients
-            const int lo = opaque(lane), col = lo & 31, hi = lo >> 5;
-            const int c = 32 * w + col;
+        {   // projections of channel c = 16 w + col; the four gradients
+            const int lo = opaque(lane), col = lo & 15, kq = lo >> 4;
+            const int c = 16 * w + col;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {                // h = 0: (p_a, g_a), h = 1: (p_b, g_b)
-                f32x16_t ap, ag;
+                f32x4_t ap[2], ag[2];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) ap[i] = ag[i] = 0.f;
+                for (int mb = 0; mb < 2; ++mb) ap[mb] = ag[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    const uint32_t o = col * kXrow + 32 * ks + 16 * hi;
-                    const bf16x8_t xhi = ld_frag(xa[0], o), xlo = ld_frag(xa[1], o);
-                    ap = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xhi, wp[16 * h + ks], ap, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xhi, wp[16 * h + 8 + ks], ag, 0, 0, 0);
-                    ap = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xlo, wp[16 * h + ks], ap, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xlo, wp[16 * h + 8 + ks], ag, 0, 0, 0);
-                }
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb) {
+                        const uint32_t o = (16 * mb + col) * kXrow + 64 * ks + 16 * kq;
+                        const bf16x8_t xhi = ld_frag(xa[0], o), xlo = ld_frag(xa[1], o);
+                        ap[mb] = mfma16(xhi, wp[2 * h][ks], ap[mb]);
+                        ag[mb] = mfma16(xhi, wp[2 * h + 1][ks], ag[mb]);
+                        ap[mb] = mfma16(xlo, wp[2 * h][ks], ap[mb]);
+                        ag[mb] = mfma16(xlo, wp[2 * h + 1][ks], ag[mb]);
+                    }
                 const float* dsrc = h ? dbs : das;
                 bf16_t* bp = h ? b_dpb : b_dpa;
                 bf16_t* bg = h ? b_dgb : b_dga;
                 const int kp = 256 * h + c, kg = 256 * h + 128 + c;
 #pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const int q0 = 8 * a + 4 * hi;
+                for (int mb = 0; mb < 2; ++mb) {
+                    const int q0 = 16 * mb + 4 * kq;
                     const float4 dd4 = *reinterpret_cast<const float4*>(&dsrc[c * kCs + q0]);
                     const float dd[4] = {dd4.x, dd4.y, dd4.z, dd4.w};
                     float vp[4], vg[4];
@@ -751,9 +756,9 @@ void k_projection_backward(
                     for (int i = 0; i < 4; ++i) {
                         const int q = q0 + i;
                         const bool m = mq[q] != 0.f;
-                        const float s = sigmoidf_(ag[4 * a + i]);
+                        const float s = sigmoidf_(ag[mb][i]);
                         vp[i] = m ? dd[i] * s : 0.f;
-                        vg[i] = m ? dd[i] * ap[4 * a + i] * s * (1.f - s) : 0.f;
+                        vg[i] = m ? dd[i] * ap[mb][i] * s * (1.f - s) : 0.f;
                         *reinterpret_cast<bf16_t*>(d4 + q * kGrow + 2 * kp) = f2bf(vp[i]);
                         *reinterpret_cast<bf16_t*>(d4 + q * kGrow + 2 * kg) = f2bf(vg[i]);
                     }
@@ -764,71 +769,69 @@ void k_projection_backward(
             }
         }
         __syncthreads();
-        {   // dx (projection part) of columns d = 32 w + col over K = 512; unit block of x
-            const int lo = opaque(lane), col = lo & 31, hi = lo >> 5;
-            f32x16_t ax;
+        {   // dx (projection part) of column d = 16 w + col over K = 512; unit block of x
+            const int lo = opaque(lane), col = lo & 15, kq = lo >> 4;
+            f32x4_t ax[2];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ax[i] = 0.f;
+            for (int mb = 0; mb < 2; ++mb) ax[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < 32; ++ks)
-                ax = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_frag(d4, col * kGrow + 32 * ks + 16 * hi), wt[ks], ax, 0, 0, 0);
-            const int to = opaque(threadIdx.x), sc = to >> 1, sh = to & 1;
-            bf16_t* xb = b_x + u * (kCh * kQ) + sc * kQ + 16 * sh;
-            reinterpret_cast<uint4*>(xb)[0] = gather_col8p(xa[0], 16 * sh, sc);
-            reinterpret_cast<uint4*>(xb)[1] = gather_col8p(xa[0], 16 * sh + 8, sc);
-            const int d = 32 * w + col;
+            for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) dxs[(8 * (i >> 2) + 4 * hi + (i & 3)) * kPq4 + d] = ax[i];
+                for (int mb = 0; mb < 2; ++mb)
+                    ax[mb] = mfma16(ld_frag(d4, (16 * mb + col) * kGrow + 64 * ks + 16 * kq), wt[ks], ax[mb]);
+            const int to = opaque(threadIdx.x), sc = to >> 2, sq = to & 3;
+            *reinterpret_cast<uint4*>(b_x + u * (kCh * kQ) + sc * kQ + 8 * sq) = gather_col8p(xa[0], 8 * sq, sc);
+            const int d = 16 * w + col;
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dxs[(16 * mb + 4 * kq + i) * kPq4 + d] = ax[mb][i];
         }
         __syncthreads();
         {   // LN_in backward of pair lp: dz = rz (dx gamma - mean(dx gamma) - xh mean(dx gamma xh))
-            const int t = opaque(threadIdx.x), lp = t >> 3, lq = t & 7;
-            float dx[16], xh[16], s1 = 0.f, s2 = 0.f;
+            const int t = opaque(threadIdx.x), lp = t >> 4, lq = t & 15;
+            float dx[8], xh[8], gam[8], s1 = 0.f, s2 = 0.f;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float4 p = *reinterpret_cast<const float4*>(&dxs[lp * kPq4 + 16 * lq + 4 * s]);
-                const float4 hh = *reinterpret_cast<const float4*>(&xhs[lp * kPq4 + 16 * lq + 4 * s]);
+            for (int s = 0; s < 2; ++s) {
+                const float4 p = *reinterpret_cast<const float4*>(&dxs[lp * kPq4 + 8 * lq + 4 * s]);
+                const float4 hh = *reinterpret_cast<const float4*>(&xhs[lp * kPq4 + 8 * lq + 4 * s]);
+                const float4 g = *reinterpret_cast<const float4*>(&prm[0][8 * lq + 4 * s]);
                 dx[4 * s] = p.x + xg[s].x;
                 dx[4 * s + 1] = p.y + xg[s].y;
                 dx[4 * s + 2] = p.z + xg[s].z;
                 dx[4 * s + 3] = p.w + xg[s].w;
-                xh[4 * s] = hh.x;
-                xh[4 * s + 1] = hh.y;
-                xh[4 * s + 2] = hh.z;
-                xh[4 * s + 3] = hh.w;
+                xh[4 * s] = hh.x; xh[4 * s + 1] = hh.y; xh[4 * s + 2] = hh.z; xh[4 * s + 3] = hh.w;
+                gam[4 * s] = g.x; gam[4 * s + 1] = g.y; gam[4 * s + 2] = g.z; gam[4 * s + 3] = g.w;
             }
             const float rz = rzs[lp];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float dh = dx[i] * prm[0][16 * lq + i];
+            for (int i = 0; i < 8; ++i) {
+                const float dh = dx[i] * gam[i];
                 s1 += dh;
                 s2 += dh * xh[i];
                 accg[i] += dx[i] * xh[i];
                 accb[i] += dx[i];
             }
-            s1 = sum_lanes8(s1) * (1.f / kCz);
-            s2 = sum_lanes8(s2) * (1.f / kCz);
-            uint32_t o[8];
+            s1 = sum_lanes16(s1) * (1.f / kCz);
+            s2 = sum_lanes16(s2) * (1.f / kCz);
+            uint32_t o[4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int d = 16 * lq + 2 * i;
-                o[i] = pack_bf16x2(rz * (dx[2 * i] * prm[0][d] - s1 - xh[2 * i] * s2),
-                                   rz * (dx[2 * i + 1] * prm[0][d + 1] - s1 - xh[2 * i + 1] * s2));
-            }
+            for (int i = 0; i < 4; ++i)
+                o[i] = pack_bf16x2(rz * (dx[2 * i] * gam[2 * i] - s1 - xh[2 * i] * s2),
+                                   rz * (dx[2 * i + 1] * gam[2 * i + 1] - s1 - xh[2 * i + 1] * s2));
             const auto rd = make_rsrc(dz + pair_of(r, k0) * kCz, (np - 1) * step2 + kCz * 2);   // pairs past N: dropped
-            bst_u4(rd, lp * step2 + 32 * lq, make_uint4(o[0], o[1], o[2], o[3]));
-            bst_u4(rd, lp * step2 + 32 * lq + 16, make_uint4(o[4], o[5], o[6], o[7]));
+            bst_u4(rd, lp * step2 + 16 * lq, make_uint4(o[0], o[1], o[2], o[3]));
         }
         load_dxg(u + gridDim.x, xg);
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        das[lp * kCz + 16 * lq + i] = accg[i];
-        dbs[lp * kCz + 16 * lq + i] = accb[i];
+    for (int i = 0; i < 8; ++i) {
+        das[lp * kCz + 8 * lq + i] = accg[i];
+        dbs[lp * kCz + 8 * lq + i] = accb[i];
     }
     __syncthreads();
-    {
+    if (t < 2 * kCz) {
         const float* src = t < kCz ? das : dbs;
         const int d = t & (kCz - 1);
         float s = 0.f;
@@ -991,11 +994,11 @@ hipError_t launch_projection_backward(const DeviceWeights& w, const void* z, con
                                       const BackwardBlocks& bb, float* partial, int grid, hipStream_t s) {
     const int64_t units = N * ((N + 31) / 32);
     if (incoming)
-        hipLaunchKernelGGL(k_projection_backward<true>, dim3(grid), dim3(kPT), 0, s, (const bf16_t*)z, mask, (int)N,
+        hipLaunchKernelGGL(k_projection_backward<true>, dim3(grid), dim3(kBT), 0, s, (const bf16_t*)z, mask, (int)N,
                            units, dA, dB, dxg, w.proj_bf, w.projt_bf, w.ln_in_w, w.ln_in_b, w.eps, (bf16_t*)dz,
                            bb.dpa, bb.dga, bb.dpb, bb.dgb, bb.xp, partial);
     else
-        hipLaunchKernelGGL(k_projection_backward<false>, dim3(grid), dim3(kPT), 0, s, (const bf16_t*)z, mask, (int)N,
+        hipLaunchKernelGGL(k_projection_backward<false>, dim3(grid), dim3(kBT), 0, s, (const bf16_t*)z, mask, (int)N,
                            units, dA, dB, dxg, w.proj_bf, w.projt_bf, w.ln_in_w, w.ln_in_b, w.eps, (bf16_t*)dz,
                            bb.dpa, bb.dga, bb.dpb, bb.dgb, bb.xp, partial);
     return hipGetLastError();
