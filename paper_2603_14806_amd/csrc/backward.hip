@@ -845,19 +845,24 @@ __global__ __launch_bounds__(kBT) void k_projection_backward(
 // V_blk[n][.] (both [128][32] bf16 unit blocks, the dot product over the 32
 // slots) for o = 0..3, reading each unit's V block once.  8 waves: wave w
 // owns rows 32 (w % 4) .. + 31 of outputs 2 (w / 4) and 2 (w / 4) + 1
-// (two 32 x 128 accumulators); the next unit's operands are loaded while
-// the current one is multiplied.  Partials: [o][grid][128][128].
+// (two 32 x 128 accumulators).  Partials: [o][grid][128][128].
+//
+// Bound by memory: 40 KB per unit.  A unit's five blocks come through a ring
+// of three 40 KB stages in LDS, filled by direct loads two units ahead (80 KB
+// in flight per compute unit), so that each byte is loaded once; with every
+// wave loading its own operands into registers a unit ahead the x block came
+// eight times, 96 KB of loads per unit (N = 1024 311 us under the profiler,
+// now about 255; N = 384 57 and 47).  Rows of 64 bytes, chunk c at slot
+// c ^ (row / 4) % 4: the 16 rows a read serves per cycle hit distinct banks.
 struct Wgrad4Args {
     const bf16_t* u[4];
 };
 
 __global__ __launch_bounds__(512) void k_wgrad4(Wgrad4Args a, const bf16_t* __restrict__ V, int64_t units,
                                                 float* __restrict__ partial) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int rl = lane & 31, hi = lane >> 5;
     const int rb = 32 * (w & 3), o0 = 2 * (w >> 2);
-    const bf16_t* U0 = a.u[o0];
-    const bf16_t* U1 = a.u[o0 + 1];
     f32x16_t acc[2][4];
 #pragma unroll
     for (int o = 0; o < 2; ++o)
@@ -865,33 +870,52 @@ __global__ __launch_bounds__(512) void k_wgrad4(Wgrad4Args a, const bf16_t* __re
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[o][j][r] = 0.f;
-    struct Ops { bf16x8_t a[2][2], b[4][2]; };
-    auto load = [&](int64_t u, Ops& p) {
-        const int64_t uu = u < units ? u : units - 1;   // past the end: a repeat, never multiplied
-        const int64_t base = uu * (kCh * kQ);
+    // Fill of a stage: 40 loads of 1 KB (16 rows of a block), five per wave.
+    constexpr int kBlk = kCh * kQ * 2, kStage = 5 * kBlk;
+    __shared__ __align__(1024) char ring[3 * kStage];
+    const uint32_t ring_base = lds_addr(ring);
+    const bf16_t* src[5];
+    uint32_t dst[5], voff[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int l = __builtin_amdgcn_readfirstlane(5 * w + i), m = l >> 3, p = l & 7;
+        src[i] = m == 0 ? a.u[0] : m == 1 ? a.u[1] : m == 2 ? a.u[2] : m == 3 ? a.u[3] : V;
+        dst[i] = (uint32_t)(m * kBlk + p * 1024);
+        voff[i] = (uint32_t)(p * 1024 + (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4));
+    }
+    auto issue = [&](int64_t u, int stage) {   // a unit past the end loads nothing (empty descriptor)
+        const bool valid = u < units;
+        const int64_t base = valid ? u * (kCh * kQ) : 0;
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            lds_load16(buffer_desc(src[i] + base, valid ? kBlk : 0), voff[i], 0, ring_base + (uint32_t)(stage * kStage) + dst[i]);
+    };
+    issue(blockIdx.x, 0);
+    issue((int64_t)blockIdx.x + gridDim.x, 1);
+    const int x = (rl >> 2) & 3;
+    const uint32_t rd[2] = {(uint32_t)(rl * 64 + ((hi ^ x) << 4)), (uint32_t)(rl * 64 + (((2 + hi) ^ x) << 4))};
+    int stage = 0;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        wait_vmcnt_pinned<5>();   // this unit's loads; the next one's stay in flight
+        __syncthreads();
+        issue(u + 2 * (int64_t)gridDim.x, stage == 0 ? 2 : stage - 1);   // into the stage read one unit ago
+        const char* st = ring + stage * kStage;
+        stage = stage == 2 ? 0 : stage + 1;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            const int64_t ra = base + (rb + rl) * kQ + 16 * ks + 8 * hi;
-            p.a[0][ks] = *reinterpret_cast<const bf16x8_t*>(U0 + ra);
-            p.a[1][ks] = *reinterpret_cast<const bf16x8_t*>(U1 + ra);
+            bf16x8_t fa[2], fb[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                p.b[j][ks] = *reinterpret_cast<const bf16x8_t*>(V + base + (32 * j + rl) * kQ + 16 * ks + 8 * hi);
-        }
-    };
-    Ops cur, nxt;
-    load(blockIdx.x, cur);
-    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        load(u + gridDim.x, nxt);
+            for (int o = 0; o < 2; ++o) fa[o] = *reinterpret_cast<const bf16x8_t*>(st + (o0 + o) * kBlk + rb * 64 + rd[ks]);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+            for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8_t*>(st + 4 * kBlk + j * 2048 + rd[ks]);
 #pragma unroll
             for (int o = 0; o < 2; ++o)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    acc[o][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[o][ks], cur.b[j][ks], acc[o][j], 0, 0, 0);
-        cur = nxt;
+                    acc[o][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[o], fb[j], acc[o][j], 0, 0, 0);
+        }
     }
+    wait_vmcnt_pinned<0>();   // nothing may still write LDS when the work-group ends
     // lane holds column 32 j + rl; register r holds row rb + 8 (r / 4) + 4 hi + r % 4
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
