@@ -1,6 +1,7 @@
 // C ABI of the triangle-multiplication library: argument validation, the
 // handle with its repacked weights, and the sequencing of the three kernels
 // K1 (projection), K2 (contraction), K3 (epilogue) on the caller's stream.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -217,29 +218,31 @@ int scratch_for(int device, void** ptr) {
     return TRI_MUL_OK;
 }
 
-// Workspace of the layer backward (bf16 path), in this order: A, B and the
-// four operands of the contraction backward (panels), C, dA, dB (result
-// layout), dx_g [N*N][c_z] fp32, five unit-block tensors, and the partial
-// sums of the weight-gradient reductions.
+// Workspace of the layer backward (bf16 path), in this order: A, B and dC
+// (panels), C (result layout), five unit-block tensors, the partial sums of
+// the two per-pair kernels, and dA, dB (result layout) with dx_g [N*N][c_z]
+// fp32.  The partials of the four projection weights are written when nothing
+// reads dA, dB and dx_g any more, so they start where dA does: with a region
+// of their own, N below about 100 needed up to 8 MB more than before the
+// epilogue's weights were summed in place (two partials per work-group of the
+// epilogue backward, where the unit blocks they replaced are small).
 struct BwdLayout {
-    size_t panel, result, dxg, block, part_eb, part_pb, part_w, part_w4, total;
-    int grid_pair;   // per-pair stages: one 512-thread work-group per compute unit
-    int grid_w4;     // the four sums over the x blocks: one 512-thread work-group per compute unit
+    size_t panel, result, dxg, block, part_eb, part_pb, part_w, tail, total;
+    int grid;   // work-groups of the per-pair stages and the weight-gradient sums: one of 512 threads per compute unit
 };
 BwdLayout bwd_layout(tri_mul_handle_t h, int64_t N) {
     BwdLayout L;
     const int64_t units = N * ((N + 31) / 32);
-    L.grid_pair = trimul::backward_grid(units, h->w.cus, 1);
+    L.grid = trimul::backward_grid(units, h->w.cus, 1);
     L.panel = round256(panel_bytes(N, h->c, h->dtype));
     L.result = round256(result_bytes(N, h->c));
     L.dxg = round256((size_t)N * (size_t)N * (size_t)h->c_z * 4);
     L.block = round256((size_t)units * 128 * 32 * 2);
-    L.part_eb = round256((size_t)L.grid_pair * 2 * 128 * 4);
-    L.part_pb = round256((size_t)L.grid_pair * 2 * 128 * 4);
-    L.part_w = round256((size_t)2 * L.grid_pair * 128 * 128 * 4);
-    L.grid_w4 = trimul::backward_grid(units, h->w.cus, 1);
-    L.part_w4 = round256((size_t)4 * L.grid_w4 * 128 * 128 * 4);
-    L.total = 3 * L.panel + 3 * L.result + L.dxg + 5 * L.block + L.part_eb + L.part_pb + L.part_w + L.part_w4;
+    L.part_eb = round256((size_t)L.grid * 2 * 128 * 4);
+    L.part_pb = round256((size_t)L.grid * 2 * 128 * 4);
+    L.part_w = round256((size_t)2 * L.grid * 128 * 128 * 4);
+    L.tail = std::max(2 * L.result + L.dxg, round256((size_t)4 * L.grid * 128 * 128 * 4));
+    L.total = 3 * L.panel + L.result + 5 * L.block + L.part_eb + L.part_pb + L.part_w + L.tail;
     return L;
 }
 
@@ -271,9 +274,6 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
         B = sB;
         C = sC;
     }
-    float* dA = reinterpret_cast<float*>(take(L.result));
-    float* dB = reinterpret_cast<float*>(take(L.result));
-    float* dxg = reinterpret_cast<float*>(take(L.dxg));
     trimul::BackwardBlocks bb;
     using trimul::bf16_t;
     bf16_t** blk[] = {&bb.dpa, &bb.dga, &bb.dpb, &bb.dgb, &bb.xp};
@@ -281,9 +281,12 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
     float* peb = reinterpret_cast<float*>(take(L.part_eb));
     float* ppb = reinterpret_cast<float*>(take(L.part_pb));
     float* pw = reinterpret_cast<float*>(take(L.part_w));
-    float* pw4 = reinterpret_cast<float*>(take(L.part_w4));
+    float* dA = reinterpret_cast<float*>(p);
+    float* dB = reinterpret_cast<float*>(p + L.result);
+    float* dxg = reinterpret_cast<float*>(p + 2 * L.result);
+    float* pw4 = dA;   // after the projection backward, the last reader of dA, dB and dxg
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int cus = h->w.cus, G = L.grid_pair, GW4 = L.grid_w4;
+    const int cus = h->w.cus, G = L.grid;
 
     hipError_t e = hipSuccess;
     if (!saved)   // recompute the forward's operands (stored transposed) and contraction
@@ -299,15 +302,15 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
     constexpr int kW = 128 * 128;
     // the four projection weights share the x blocks: one pass over them
     const bf16_t* const u4[4] = {bb.dpa, bb.dga, bb.dpb, bb.dgb};
-    if (e == hipSuccess) e = trimul::launch_wgrad4(u4, bb.xp, N, pw4, GW4, s);
-    const size_t p4 = (size_t)GW4 * kW;
+    if (e == hipSuccess) e = trimul::launch_wgrad4(u4, bb.xp, N, pw4, G, s);
+    const size_t p4 = (size_t)G * kW;
     const trimul::SumTask sums[] = {
         {pw, g->w_o, G, kW, kW, 0},
         {pw + (size_t)G * kW, g->w_g, G, kW, kW, 0},
-        {pw4, g->w_a, GW4, kW, kW, 0},
-        {pw4 + p4, g->w_ga, GW4, kW, kW, 0},
-        {pw4 + 2 * p4, g->w_b, GW4, kW, kW, 0},
-        {pw4 + 3 * p4, g->w_gb, GW4, kW, kW, 0},
+        {pw4, g->w_a, G, kW, kW, 0},
+        {pw4 + p4, g->w_ga, G, kW, kW, 0},
+        {pw4 + 2 * p4, g->w_b, G, kW, kW, 0},
+        {pw4 + 3 * p4, g->w_gb, G, kW, kW, 0},
         {peb, g->ln_out_w, G, 256, 128, 0},
         {peb + 128, g->ln_out_b, G, 256, 128, 0},
         {ppb, g->ln_in_w, G, 256, 128, 0},
