@@ -192,7 +192,10 @@ void k_triattn(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
         };
         if (mask != nullptr || k0 + (c + 1) * kKc > kend) scores(true);
         else scores(false);
-        load_bias(c + 1, bb);                                 // into the released registers
+        // The next chunk's bias goes into the released registers: with fp32 output
+        // at once, with bf16 output after the PV product (n = 1024 without a mask:
+        // 1594 us at once, 1612 after it; bf16 1463 and 1425)
+        if constexpr (kHiLo) load_bias(c + 1, bb);
         cm = fmaxf(cm, xor32(cm));
         // The state is relative to the running maximum M itself: the largest
         // weight is then exactly 1 and loses nothing to its bf16 rounding.  (A
@@ -246,6 +249,7 @@ void k_triattn(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                 if constexpr (kHiLo)
                     o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8_t, make_uint4(pl[0], pl[1], pl[2], pl[3])), o, 0, 0, 0);
             }
+        if constexpr (!kHiLo) load_bias(c + 1, bb);
         // no barrier here: the next chunk stages into the other buffer, and the
         // one after that only once every wave has passed the next barrier
     }
