@@ -70,6 +70,16 @@ int tri_mul_check_contract_loads(int a_mode, int b_mode, int64_t M, int64_t N, i
 int tri_mul_check_contract_result(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_channels,
                                   tri_mul_load_check_t* out);
 
+/*
+ * The side of the square output tiles that the contraction works in for
+ * `batch` products of M rows by N columns on a device with `cus` compute
+ * units: 256 for bf16 storage, 64 or 128 for float32 (by size), in *side.
+ * Host only; tests use it to state which kernel instance their sizes reach.
+ * Returns TRI_MUL_OK, or TRI_MUL_EINVAL for null `side`, a bad dtype or sizes
+ * outside [1, 65536].
+ */
+int tri_mul_check_contract_tile(int dtype, int64_t M, int64_t N, int batch, int cus, int* side);
+
 #ifdef __cplusplus
 }
 #endif

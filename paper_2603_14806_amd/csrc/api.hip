@@ -1224,6 +1224,15 @@ int tri_mul_check_contract_loads(int a_mode, int b_mode, int64_t M, int64_t N, i
     return ok();
 }
 
+int tri_mul_check_contract_tile(int dtype, int64_t M, int64_t N, int batch, int cus, int* side) {
+    if (!side) return fail(TRI_MUL_EINVAL, "null side");
+    if (dtype != TRI_MUL_F32 && dtype != TRI_MUL_BF16) return fail(TRI_MUL_EINVAL, "bad dtype %d", dtype);
+    if (M < 1 || N < 1 || batch < 1 || cus < 1 || M > kMaxN || N > kMaxN)
+        return fail(TRI_MUL_EINVAL, "sizes must lie in [1, %lld]", (long long)kMaxN);
+    *side = dtype == TRI_MUL_F32 ? trimul::contract_f32_tile(M, N, batch, cus) : trimul::kBlkRows;
+    return ok();
+}
+
 int tri_mul_check_contract_result(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_channels,
                                   tri_mul_load_check_t* out) {
     if (!out) return fail(TRI_MUL_EINVAL, "null out");

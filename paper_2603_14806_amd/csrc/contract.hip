@@ -776,19 +776,23 @@ hipError_t launch_stage_kmask(const uint8_t* mask, int64_t klen, uint8_t* dst, h
     return hipGetLastError();
 }
 
+// Tiles of 128 halve the L2 traffic of a product, tiles of 64 give four times
+// the work-groups and pad less.  128 from 16 tiles per compute unit on where
+// its padding costs at most 5% (N = 1024: 2.01 against 2.18 ms; equal at N =
+// 512; at N = 384 148 against 128 us, at N = 700 792 against 719, at N = 64 8.9
+// against 7.5).
+int contract_f32_tile(int64_t M, int64_t N, int batch, int cus) {
+    const int64_t t1 = (M + 127) / 128 * ((N + 127) / 128), t2 = (M + 63) / 64 * ((N + 63) / 64);
+    return t1 * batch >= 16 * (int64_t)cus && 80 * t1 <= 21 * t2 ? 128 : 64;
+}
+
 hipError_t launch_contract(int dtype, int blocked, const void* A, const void* B, float* C, int64_t M,
                            int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int64_t sA,
                            int64_t sB, int64_t sC, int batch, int accumulate, const uint8_t* kmask, int cus,
                            hipStream_t s) {
     if (dtype == 0) {
-        // Tiles of 128 halve the L2 traffic of a product, tiles of 64 give four
-        // times the work-groups and pad less.  128 from 16 tiles per compute
-        // unit on where its padding costs at most 5% (N = 1024: 2.01 against
-        // 2.18 ms; equal at N = 512; at N = 384 148 against 128 us, at N = 700
-        // 792 against 719, at N = 64 8.9 against 7.5).
-        const int64_t t1 = (M + 127) / 128 * ((N + 127) / 128), t2 = (M + 63) / 64 * ((N + 63) / 64);
-        const bool wide = t1 * batch >= 16 * (int64_t)cus && 80 * t1 <= 21 * t2;
-        const int T = wide ? 128 : 64;
+        const int T = contract_f32_tile(M, N, batch, cus);
+        const bool wide = T == 128;
         const int tm = (int)((M + T - 1) / T), tn = (int)((N + T - 1) / T);
 #define K2_F32(T_, BL_)                                                                                             \
     hipLaunchKernelGGL((k2_contract_f32<T_, BL_>), dim3((unsigned)(tm * tn * batch)), dim3(256), 0, s,              \

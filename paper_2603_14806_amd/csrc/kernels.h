@@ -119,6 +119,9 @@ hipError_t launch_contract(int dtype, int blocked, const void* A, const void* B,
                            int64_t sB, int64_t sC, int batch, int accumulate, const uint8_t* kmask, int cus,
                            hipStream_t s);
 
+// Side of the output tiles of the fp32 contraction: 64 or 128.
+int contract_f32_tile(int64_t M, int64_t N, int batch, int cus);
+
 // K3: LN_out + output projection + sigmoid gate + pair mask -> out [rows][cols][c_z].
 hipError_t launch_epilogue(int dtype, int out_dtype, const DeviceWeights& w, const EpilogueArgs& a,
                            hipStream_t s);

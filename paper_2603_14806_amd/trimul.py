@@ -122,6 +122,8 @@ SIGNATURES = {
                                                     ctypes.c_int, ctypes.POINTER(LoadCheck)]),
     "tri_mul_check_contract_result": (ctypes.c_int, [_i64, _i64, ctypes.c_int, ctypes.c_uint64, ctypes.c_int,
                                                       ctypes.POINTER(LoadCheck)]),
+    "tri_mul_check_contract_tile": (ctypes.c_int, [ctypes.c_int, _i64, _i64, ctypes.c_int, ctypes.c_int,
+                                                   ctypes.POINTER(ctypes.c_int)]),
     "tri_attn_state_size": (ctypes.c_int, [ctypes.POINTER(TriAttnView), ctypes.POINTER(ctypes.c_size_t)]),
     "tri_attn_chunk": (ctypes.c_int, [ctypes.POINTER(TriAttnView), _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "tri_attn_forward": (ctypes.c_int, [_vp, _vp, _vp, _vp, _vp, _i64, _i64, ctypes.c_int32, _i64, ctypes.c_int32,
@@ -682,3 +684,11 @@ def check_contract_result(M, N, batch=128, c_bytes=0, all_channels=False):
     out = LoadCheck()
     _check(lib().tri_mul_check_contract_result(M, N, batch, c_bytes, int(all_channels), ctypes.byref(out)))
     return {name: getattr(out, name) for name, _ in LoadCheck._fields_}
+
+
+def check_contract_tile(dtype, M, N, batch=128, cus=256):
+    """Side of the output tiles the contraction uses for these products
+    (tri_mul_check_contract_tile); dtype "f32" or "bf16"."""
+    side = ctypes.c_int()
+    _check(lib().tri_mul_check_contract_tile(DTYPE_CODE[dtype], M, N, batch, cus, ctypes.byref(side)))
+    return side.value

@@ -12,15 +12,20 @@ pytestmark = [pytest.mark.gpu, needs_gpu]
 CHANNELS = [0, 63, 127]   # the addressing is the same in every channel apart from its offset
 
 
+def _tile(M, N):
+    return T.check_contract_tile("f32", M, N, cus=torch.cuda.get_device_properties(0).multi_processor_count)
+
+
 def _ints(shape, seed):
     g = torch.Generator().manual_seed(seed)
     return torch.randint(-4, 5, shape, generator=g).float()
 
 
-@pytest.mark.parametrize("N", [1, 31, 64, 97, 769])   # 769: tiles of 128
-def test_contract_f32_exact_with_nan_padding(N):
+@pytest.mark.parametrize("N,tile", [(1, 64), (31, 64), (64, 64), (97, 64), (769, 64), (705, 128)])
+def test_contract_f32_exact_with_nan_padding(N, tile):
     """Small integers are exact in fp32 in any order of the sums; the panels'
     padding rows and k hold NaN."""
+    assert _tile(N, N) == tile
     say(f"f32 contract exact N={N}")
     layer, _ = make_layer("f32")
     A, B = _ints((128, N, N), N), _ints((128, N, N), N + 1)
@@ -37,10 +42,11 @@ def test_contract_f32_exact_with_nan_padding(N):
     np.testing.assert_array_equal(host(T.result_to_dense(C, N)[CHANNELS]).transpose(1, 2, 0), ref)
 
 
-@pytest.mark.parametrize("rows,cols,klen", [(1, 130, 33), (100, 65, 70), (900, 770, 45)])   # the last: tiles of 128
-def test_block_accumulate_f32_row_major_exact(rows, cols, klen):
+@pytest.mark.parametrize("rows,cols,klen,tile", [(1, 130, 33, 64), (100, 65, 70, 64), (900, 770, 45, 64), (833, 705, 45, 128)])
+def test_block_accumulate_f32_row_major_exact(rows, cols, klen, tile):
     """Row-major panels over two steps into one accumulator: NaN past klen in
     the row padding and at masked k, exact sums elsewhere."""
+    assert _tile(rows, cols) == tile
     say(f"f32 block accumulate exact {rows} x {cols} x {klen}")
     layer, _ = make_layer("f32")
     ld = -(-klen // 8) * 8 + 8

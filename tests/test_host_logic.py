@@ -66,3 +66,17 @@ def test_peaks():
     assert perf.PEAK_HBM_GBS == 8000.0
     assert perf.PEAK_LANE_OPS == 256 * 4 * 32 * 2.4e9
     assert abs(perf.PEAK_LANE_OPS / perf.TRIATTN_SLOTS / 1e12 - 9.25) < 0.01
+
+
+def test_fp32_contraction_tiles():
+    """Tiles of 128 from 16 of them per compute unit on, where they pad at
+    most 5% more than tiles of 64; 256 for bf16 storage."""
+    from paper_2603_14806_amd import trimul as T
+    for N in range(1, 1100):
+        t1, t2 = (-(-N // 128)) ** 2, (-(-N // 64)) ** 2
+        wide = 128 * t1 >= 16 * 256 and 4 * t1 <= 1.05 * t2 + 1e-9
+        assert T.check_contract_tile("f32", N, N) == (128 if wide else 64), N
+        assert T.check_contract_tile("bf16", N, N) == 256
+    assert T.check_contract_tile("f32", 833, 705) == 128 and T.check_contract_tile("f32", 900, 770) == 64
+    with pytest.raises(T.TriMulError):
+        T.check_contract_tile("f32", 0, 5)
