@@ -57,8 +57,11 @@ int tri_mul_check_contract_loads(int a_mode, int b_mode, int64_t M, int64_t N, i
  * the pair-blocked result layout (tri_mul_contract): M rows, N columns,
  * `batch` channels, element (b, i, j) at ((i * J + j / 32) * batch + b) * 32
  * + j % 32 floats with J = ceil(N / 32), c_bytes allocated.  Each MFMA wave
- * reads (when accumulating) and writes its 64 x 128 part of a tile through
- * one buffer descriptor per 32-column block.  Reports in *out: tiles, the
+ * reads (when accumulating) and writes its part of a tile (64 x 128 of a whole
+ * one) through one buffer descriptor per 32-column block.  Blocked and
+ * transposed operands cut a ragged side into tiles in different ways; every
+ * pairing of the two is walked.  Reports in *out (tiles, loads and elems of
+ * two blocked operands, the violations of all pairings): tiles, the
  * 64-lane register groups visited (loads), the elements with row < M and
  * column < N visited (elems), descriptors reaching outside c_bytes
  * (bad_desc), and accesses at an address other than the layout's, inside

@@ -930,16 +930,21 @@ void k2_check_c_sides(const K2Side& sm, const K2Side& sn, int64_t M, int64_t N, 
 
 void k2_check_c(int64_t M, int64_t N, int batch, uint64_t c_bytes, int all_channels, K2CheckCounts& n) {
     n = K2CheckCounts{};
-    // the tile sides of blocked operands, then those of transposed and
-    // row-major ones where they differ
-    k2_check_c_sides(k2_side(kK2Blocked, (int)M), k2_side(kK2Blocked, (int)N), M, N, batch, c_bytes, all_channels, n);
-    const K2Side em = k2_side(kK2Transposed, (int)M), en = k2_side(kK2Transposed, (int)N);
-    if (em.units % 4 == 0 && en.units % 4 == 0) return;
-    K2CheckCounts e;
-    k2_check_c_sides(em, en, M, N, batch, c_bytes, all_channels, e);
-    if (e.elems != n.elems) ++n.bad_elem;
-    n.bad_desc += e.bad_desc;
-    n.bad_elem += e.bad_elem;
+    // the tile sides of two blocked operands, then every other pairing of
+    // blocked and transposed sides that differs from those before it
+    const K2Side sm[2] = {k2_side(kK2Blocked, (int)M), k2_side(kK2Transposed, (int)M)};
+    const K2Side sn[2] = {k2_side(kK2Blocked, (int)N), k2_side(kK2Transposed, (int)N)};
+    k2_check_c_sides(sm[0], sn[0], M, N, batch, c_bytes, all_channels, n);
+    const bool dm = sm[0].units % 4 != 0 && sm[0].tiles > 1, dn = sn[0].units % 4 != 0 && sn[0].tiles > 1;
+    for (int ta = 0; ta < 2; ++ta)
+        for (int tb = 0; tb < 2; ++tb) {
+            if ((!ta && !tb) || (ta && !dm) || (tb && !dn)) continue;
+            K2CheckCounts e;
+            k2_check_c_sides(sm[ta], sn[tb], M, N, batch, c_bytes, all_channels, e);
+            if (e.elems != n.elems) ++n.bad_elem;
+            n.bad_desc += e.bad_desc;
+            n.bad_elem += e.bad_elem;
+        }
 }
 
 void k2_check_loads(int a_mode, int b_mode, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t sA,
