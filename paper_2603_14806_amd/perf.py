@@ -43,17 +43,16 @@ PEAK_LANE_OPS = 256 * 4 * 32 * 2.4e9
 def backward_layer_work(N, c_z=128, c=128, recompute=True):
     """One direction of the layer backward: the MFMA flops of its N^3 products
     (the recomputed forward contraction unless the forward's state is passed
-    in, dA and dB) and the HBM bytes of its per-pair kernels in the unfused
-    form, every weight-gradient operand written once and read once (per pair:
-    projection recompute 768 B (recompute only), epilogue backward 3072 B,
-    projection backward 3328 B, six weight-gradient sums 6 x 512 B = 10240 B
-    at c_z = c = 128 with the recompute; the products read their transposed
-    operands in place).  The library sums the two weights of the epilogue in
-    place and so moves 2048 B less; the figures keep this yardstick."""
+    in, dA and dB) and the HBM bytes its per-pair kernels move, per pair:
+    projection recompute 768 B (recompute only), epilogue backward 2048 B (C,
+    z and fp32 dout read, bf16 dC and fp32 dx_g written; its two weights are
+    summed in place), projection backward 3328 B, weight gradients of the four
+    projections 1280 B (their five blocks read once) = 7424 B at c_z = c = 128
+    with the recompute; the products read their transposed operands in place."""
     mfma = (3 if recompute else 2) * 2.0 * N ** 3 * c
     per_pair = (c_z * 2 + 2 * c * 2 if recompute else 0) \
-        + (c * 4 + c_z * 2 + c_z * 4 + c * 2 + c_z * 4 + 4 * 2 * c) \
-        + (2 * c * 4 + c_z * 2 + c_z * 4 + c_z * 2 + 5 * 2 * c) + 6 * 4 * c
+        + (c * 4 + c_z * 2 + c_z * 4 + c * 2 + c_z * 4) \
+        + (2 * c * 4 + c_z * 2 + c_z * 4 + c_z * 2 + 5 * 2 * c) + 5 * 2 * c
     return {"mfma_flops": mfma, "hbm_bytes": float(per_pair) * N * N,
             "floor_ms": 1e3 * (mfma / (PEAK_BF16_TFLOPS * 1e12) + per_pair * N * N / (PEAK_HBM_GBS * 1e9))}
 

@@ -46,15 +46,16 @@ def test_byte_model_matches_the_tensors_moved():
 
 
 def test_backward_model():
-    """The saved-forward backward: two N^3 products and 10240 bytes per pair;
-    the recomputing one adds a third product and 768 bytes per pair."""
+    """The recomputing backward: three N^3 products and 7424 bytes per pair
+    (768 + 2048 + 3328 + 1280, as the kernels move them); the saved-forward
+    one has a product and 768 bytes per pair less."""
     s = perf.backward_layer_work(4096, recompute=False)
     r = perf.backward_layer_work(4096, recompute=True)
     assert s["mfma_flops"] == 2 * 2 * 4096 ** 3 * 128
     assert r["mfma_flops"] == 3 * 2 * 4096 ** 3 * 128
     per_pair_saved = s["hbm_bytes"] / 4096 ** 2
     per_pair_full = r["hbm_bytes"] / 4096 ** 2
-    assert per_pair_full == 10240
+    assert per_pair_full == 768 + 2048 + 3328 + 1280
     assert per_pair_full - per_pair_saved == 128 * 2 + 2 * 128 * 2
     floor = 1e3 * (s["mfma_flops"] / (perf.PEAK_BF16_TFLOPS * 1e12) + s["hbm_bytes"] / (perf.PEAK_HBM_GBS * 1e9))
     assert abs(s["floor_ms"] - floor) < 1e-9
