@@ -47,11 +47,6 @@ __device__ __forceinline__ float sum_lanes8(float v) {
     v += dpp_mov<0x141>(v);   // row_half_mirror
     return v;
 }
-__device__ __forceinline__ float sum_lanes4(float v) {
-    v += dpp_mov<0xb1>(v);
-    v += dpp_mov<0x4e>(v);
-    return v;
-}
 
 // Element e (a compile-time constant after unrolling) of a float4.
 __device__ __forceinline__ float f4_get(const float4& v, int e) {

@@ -115,7 +115,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(768, 768), amdgpu_waves_pe
 void k2_contract_ws(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, float* __restrict__ C, int M,
                     int N, int K, int lda, int ldb, int64_t ldc, int64_t sA, int64_t sB, int64_t sC, int total,
                     int accumulate, const uint8_t* __restrict__ kmask, int pace) {
-    constexpr int BM = kK2Tile, MI = 2;
+    constexpr int BM = kK2Tile;
     constexpr int A_ST = BM * ROWB, ST_BYTES = A_ST + B_ST;
     constexpr int STAGES = kLdsBytes / ST_BYTES;  // 5
     constexpr int LOADS = 2 * kK2LoadsPerOperand;  // direct-to-LDS loads per loader wave per step

@@ -162,7 +162,7 @@ __device__ __forceinline__ uint32_t yoff(int p, int chunk) {
     return (uint32_t)(p * kYRow + ((chunk ^ (p & 15)) << 4));
 }
 
-template <typename TO, bool VEC_C, bool CBLK>
+template <typename TO, bool VEC_C>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void k3_epilogue_mfma(EpilogueArgs a, int nchunk, int64_t nunits, const bf16_t* __restrict__ wepi,
                       const float* __restrict__ lnin_w, const float* __restrict__ lnin_b,
@@ -200,22 +200,8 @@ void k3_epilogue_mfma(EpilogueArgs a, int nchunk, int64_t nunits, const bf16_t* 
         const uint32_t uq = (uint32_t)u / (uint32_t)nchunk;   // units < 2^31
         const int64_t i = uq, j0 = (int64_t)((uint32_t)u - uq * (uint32_t)nchunk) * kP3;
         const int np = (int)min<int64_t>(kP3, a.cols - j0);
-        if (CBLK) {   // the unit's 128 channels x 32 pairs are one contiguous block
-            const float4* blk = reinterpret_cast<const float4*>(a.C + result_off(nchunk, kCh, 0, i, j0));
 #pragma unroll
-            for (int s2 = 0; s2 < 4; ++s2) {
-                float4 v = blk[t + 256 * s2];
-                if (4 * cj + 4 > np) {   // pairs past the end of the row are padding
-                    if (4 * cj + 0 >= np) v.x = 0.f;
-                    if (4 * cj + 1 >= np) v.y = 0.f;
-                    if (4 * cj + 2 >= np) v.z = 0.f;
-                    if (4 * cj + 3 >= np) v.w = 0.f;
-                }
-                cv[s2] = v;
-            }
-        }
-#pragma unroll
-        for (int s2 = 0; s2 < 4 && !CBLK; ++s2) {
+        for (int s2 = 0; s2 < 4; ++s2) {
             const float* src = a.C + (int64_t)((t >> 3) + 32 * s2) * a.sc + i * a.ldc + j0 + 4 * cj;
             if (VEC_C && 4 * cj + 4 <= np) {
                 cv[s2] = *reinterpret_cast<const float4*>(src);
@@ -662,10 +648,10 @@ hipError_t launch_mfma(const DeviceWeights& w, const EpilogueArgs& a, hipStream_
                            a.mask ? a.mask + lo : nullptr, coff, roff, a.mask ? (ce > re ? ce : re) : 0u, (int)a.cols,
                            (int)nunits, (TO*)a.out, w.epi_bf, w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
     } else if (vec)
-        hipLaunchKernelGGL((k3_epilogue_mfma<TO, true, false>), dim3(g), dim3(256), 0, s, a, nchunk, nunits, w.epi_bf,
+        hipLaunchKernelGGL((k3_epilogue_mfma<TO, true>), dim3(g), dim3(256), 0, s, a, nchunk, nunits, w.epi_bf,
                            w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
     else
-        hipLaunchKernelGGL((k3_epilogue_mfma<TO, false, false>), dim3(g), dim3(256), 0, s, a, nchunk, nunits, w.epi_bf,
+        hipLaunchKernelGGL((k3_epilogue_mfma<TO, false>), dim3(g), dim3(256), 0, s, a, nchunk, nunits, w.epi_bf,
                            w.ln_in_w, w.ln_in_b, w.ln_out_w, w.ln_out_b, w.eps);
     return hipGetLastError();
 }
