@@ -935,12 +935,12 @@ __global__ __launch_bounds__(512) void k_wgrad4(Wgrad4Args a, const bf16_t* __re
 // in[g * stride + i], for several outputs in one launch.  A work-group takes
 // 32 consecutive outputs of one sum (one 128-byte line of every partial): 32
 // slices of 8 lanes each add every 32nd partial, then the slices are added in
-// order, so the result does not depend on the grid and is the same every
-// time.  Bound by the latency of reading the partials (16 MB for one 128 x
-// 128 gradient): one thread per output, which walked all of them alone, kept
-// 64 work-groups on a serial chain of 256 to 512 loads, 96 us a sum and
-// 870 us of a backward call; now the two launches of a call take 26 us
-// (N = 384, 256 compute units).
+// order, so the result is the same every time for one number of compute units
+// (each partial is the sum of one work-group's units).  Bound by the latency of
+// reading the partials (16 MB for one 128 x 128 gradient): one thread per
+// output, which walked all of them alone, kept 64 work-groups on a serial chain
+// of 256 to 512 loads, 96 us a sum and 870 us of a backward call; now a call's
+// one launch for all ten sums takes 20 us (N = 384, 256 compute units).
 __global__ __launch_bounds__(256) void k_sum_parts(SumTasks a) {
     __shared__ __align__(16) float4 red[32][8];
     int i = 0;

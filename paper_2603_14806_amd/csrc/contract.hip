@@ -714,7 +714,11 @@ bool cblocked_fits(int64_t N, int batch) {
 // memset, so that the sequence can be captured in a graph).  It pays only for
 // long tiles: shorter ones drift apart less than the wait and the reset cost
 // (N = 4096 13.67 ms paced, 13.96 not; N = 2048 1954 against 1910 us, N = 1300
-// 695 against 649, N = 512 55 against 51).
+// 695 against 649, N = 512 55 against 51).  The line itself was put between the
+// two.  Measured around it since: square products lose up to about 3900 (N =
+// 3072 6.03 ms paced, 5.87 not; 3584 9.48 and 9.18; 3840 11.56 and 11.28) and gain
+// above (5120 26.9 and 27.3; 6144 46.0 and 47.9); an accumulating ring step of
+// 3000 tokens gains (6.49 against 6.73), one of 2560 loses (4.18 against 3.93).
 constexpr int64_t kPaceMinK = 3072;
 namespace {
 int pace_launch(int grid, int total, int64_t K, hipStream_t s) {

@@ -100,7 +100,9 @@ struct EpilogueArgs {
 
 // K1: LN_in + gated projections + pair mask -> channel-major operands A, B in
 // the blocked panel layout (common.h) of N rows and K = N.  Padding rows are
-// left untouched; the k padding of a row's last k-step is written with zeros.
+// left untouched; the k padding of a row's last k-step is written with zeros by
+// the bf16 projection and left untouched by the fp32 one (both contractions
+// drop it themselves).
 // The bf16 projection of an M x K operand pair (A, B in the blocked layout of
 // panel_geom(M, K)): operand row i, contraction index k is pair (i, k) of z
 // (outgoing) or (k, i) (incoming), z rows ldz pairs apart; mask: token mask

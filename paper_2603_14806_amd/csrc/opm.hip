@@ -5,10 +5,10 @@
 //     O[(i, c)][(j, d)] = sum_s m_si m_sj a_sic b_sjd,
 //
 // is one NT product with M = rows * D, N = cols * D, K = slen (both operands
-// given transposed, which is the input's own order), and the pair
-// counts n_ij = sum_s m_si m_sj another with M = rows, N = cols (0/1
-// operands: exact in fp32 up to 2^24); both run on the contraction kernel
-// (k2_contract_ws), accumulating over the steps of a tile.
+// given transposed, which is the input's own order) on the contraction kernel
+// (k2_contract_ws); the pair counts n_ij = sum_s m_si m_sj are the set bits
+// that two tokens' mask words share (k_opm_count; whole numbers, exact in fp32
+// up to 2^24).  Both accumulate over the steps of a tile.
 #include "common.h"
 #include "kernels.h"
 
