@@ -219,13 +219,14 @@ int scratch_for(int device, void** ptr) {
 }
 
 // Workspace of the layer backward (bf16 path), in this order: A, B and dC
-// (panels), C (result layout), five unit-block tensors, the partial sums of
-// the two per-pair kernels, and dA, dB (result layout) with dx_g [N*N][c_z]
-// fp32.  The partials of the four projection weights are written when nothing
-// reads dA, dB and dx_g any more, so they start where dA does: with a region
-// of their own, N below about 100 needed up to 8 MB more than before the
-// epilogue's weights were summed in place (two partials per work-group of the
-// epilogue backward, where the unit blocks they replaced are small).
+// (panels), C, dA, dB (result layout), dx_g [N*N][c_z] fp32, five unit-block
+// tensors, and the partial sums of the two per-pair kernels.  The partials of
+// the four projection weights are written when nothing reads dA, dB and dx_g
+// any more, so they start where dA does: with a region of their own, N below
+// about 100 needed up to 8 MB more than before the epilogue's weights were
+// summed in place (two partials per work-group of the epilogue backward, where
+// the unit blocks they replaced are small).  The order matters a little: with
+// the unit blocks before dA N = 1024 took 1% longer.
 struct BwdLayout {
     size_t panel, result, dxg, block, part_eb, part_pb, part_w, tail, total;
     int grid;   // work-groups of the per-pair stages and the weight-gradient sums: one of 512 threads per compute unit
@@ -274,6 +275,10 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
         B = sB;
         C = sC;
     }
+    float* dA = reinterpret_cast<float*>(take(L.tail));
+    float* dB = dA + L.result / 4;
+    float* dxg = dB + L.result / 4;
+    float* pw4 = dA;   // after the projection backward, the last reader of dA, dB and dxg
     trimul::BackwardBlocks bb;
     using trimul::bf16_t;
     bf16_t** blk[] = {&bb.dpa, &bb.dga, &bb.dpb, &bb.dgb, &bb.xp};
@@ -281,10 +286,6 @@ int run_backward(tri_mul_handle_t h, const void* z, const uint8_t* mask, int64_t
     float* peb = reinterpret_cast<float*>(take(L.part_eb));
     float* ppb = reinterpret_cast<float*>(take(L.part_pb));
     float* pw = reinterpret_cast<float*>(take(L.part_w));
-    float* dA = reinterpret_cast<float*>(p);
-    float* dB = reinterpret_cast<float*>(p + L.result);
-    float* dxg = reinterpret_cast<float*>(p + 2 * L.result);
-    float* pw4 = dA;   // after the projection backward, the last reader of dA, dB and dxg
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int cus = h->w.cus, G = L.grid;
 
