@@ -141,8 +141,9 @@ void k1_project_f32(const float* __restrict__ z, const uint8_t* __restrict__ mas
 // z and the token mask reach LDS through a 3-stage ring filled by
 // direct-to-LDS buffer loads two lines ahead of the line being computed, so
 // the HBM latency of z hides behind two lines of work.  Every wave issues
-// the same number of vector-memory instructions per line (3 loads, 4 stores,
-// tails included), which makes the vmcnt waits exact constants.
+// the same number of vector-memory instructions per line (3 loads, 2 without a
+// mask, and 4 stores, tails included), which makes the vmcnt waits exact
+// constants.
 //
 // Precision: the matrix cores take fp16 operands, 11 significant bits
 // against bf16's 8.  The weights (bf16 values) and the LayerNormed x
@@ -169,9 +170,11 @@ __device__ __forceinline__ uint32_t xoff(int p, int chunk) {
 // The operands are M x K: operand row i (M of them) and contraction index k
 // (K).  Outgoing, pair (i, k) is z[i][k]; incoming, pair (k, i) is z[k][i];
 // z rows are ldz pairs apart (the full update: M = K = ldz = N; a device
-// tile: its rows and columns).  mask: token bytes (null: all real), the
-// k-range's at koff, the operand rows' at roff; mrange bytes are readable.
-template <bool INCOMING>
+// tile: its rows and columns).  MASK: mask holds token bytes, the k-range's at
+// koff, the operand rows' at roff; mrange bytes are readable.  Without one every
+// token is real and no mask load is issued (loads through an empty descriptor in
+// its place cost 0.2 to 0.5% at N = 4096).
+template <bool INCOMING, bool MASK>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
 void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __restrict__ mask, uint32_t koff,
                      uint32_t roff, uint32_t mrange, int M, int K, int nlines, const uint16_t* __restrict__ wproj,
@@ -219,10 +222,13 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
         const uint32_t st = ring_base + (uint32_t)(stage * kSt);
         lds_load16(rz, dv0, 0, st + g * 2048);
         lds_load16(rz, dv1, 0, st + g * 2048 + 1024);
-        const v4i_t rm = buffer_desc(mask, valid ? mrange : 0u);
-        const uint32_t mo = lane < 32 ? koff + (uint32_t)(k0 + lane) : lane == 32 ? roff + (uint32_t)r : 0xfffffff0u;
-        lds_load_u8(rm, mo, st + kZSt + g * 256);
+        if constexpr (MASK) {
+            const v4i_t rm = buffer_desc(mask, valid ? mrange : 0u);
+            const uint32_t mo = lane < 32 ? koff + (uint32_t)(k0 + lane) : lane == 32 ? roff + (uint32_t)r : 0xfffffff0u;
+            lds_load_u8(rm, mo, st + kZSt + g * 256);
+        }
     };
+    constexpr int kLd = MASK ? 3 : 2;   // loads per line and wave
     issue(first, 0);
     issue(first + G, 1);
 
@@ -246,11 +252,11 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
     int stage = 0;
     for (int it = 0, line = first; line < nlines; ++it, line += G) {
         // Vector-memory instructions issued after this line's loads: the
-        // next line's loads (3) and, from the second line on, the 4 stores
-        // of every line in between.
-        if (it == 0) wait_vmcnt_pinned<3>();
-        else if (it == 1) wait_vmcnt_pinned<3 + 4>();
-        else wait_vmcnt_pinned<3 + 4 + 4>();
+        // next line's loads and, from the second line on, the 4 stores of
+        // every line in between.
+        if (it == 0) wait_vmcnt_pinned<kLd>();
+        else if (it == 1) wait_vmcnt_pinned<kLd + 4>();
+        else wait_vmcnt_pinned<kLd + 4 + 4>();
         __syncthreads();
         issue(line + 2 * G, stage == 0 ? 2 : stage - 1);   // into the stage read one line ago
         const char* zs = ring + stage * kSt;
@@ -297,7 +303,7 @@ void k1_project_mfma(const bf16_t* __restrict__ z, int ldz, const uint8_t* __res
         // z would have left.
         const int kc = line / M, r0 = line - kc * M, k0 = kc * kP1;
         const uint32_t* ms = reinterpret_cast<const uint32_t*>(zs + kZSt + g * 256);   // this wave's copy
-        const uint32_t keep = k0 + lp < K && (!mask || (ms[lp] != 0 && ms[32] != 0)) ? 0xffffffffu : 0u;
+        const uint32_t keep = k0 + lp < K && (!MASK || (ms[lp] != 0 && ms[32] != 0)) ? 0xffffffffu : 0u;
         uint4 x0 = __builtin_bit_cast(uint4, xh[0]), x1 = __builtin_bit_cast(uint4, xh[1]);
         x0 = make_uint4(x0.x & keep, x0.y & keep, x0.z & keep, x0.w & keep);
         x1 = make_uint4(x1.x & keep, x1.y & keep, x1.z & keep, x1.w & keep);
@@ -366,14 +372,15 @@ hipError_t launch_project_mfma(const DeviceWeights& w, const void* z, int64_t ld
     const uint32_t koff = (uint32_t)(k0 - lo), roff = (uint32_t)(m0 - lo);
     const uint8_t* mk = mask ? mask + lo : nullptr;
     const uint32_t mrange = mask ? std::max(koff + (uint32_t)K, roff + (uint32_t)M) : 0u;
-    if (incoming)
-        hipLaunchKernelGGL((k1_project_mfma<true>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, mk, koff, roff,
-                           mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps, w.k1s,
-                           (bf16_t*)A, (bf16_t*)B);
-    else
-        hipLaunchKernelGGL((k1_project_mfma<false>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, mk, koff, roff,
-                           mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps, w.k1s,
-                           (bf16_t*)A, (bf16_t*)B);
+#define K1_BF16(IN_, MASK_)                                                                                        \
+    hipLaunchKernelGGL((k1_project_mfma<IN_, MASK_>), dim3(g), dim3(256), 0, s, (const bf16_t*)z, (int)ldz, mk, koff, \
+                       roff, mrange, (int)M, (int)K, nlines, w.proj_h, w.ln_in_w_h, w.ln_in_b_h, w.eps, w.k1s,      \
+                       (bf16_t*)A, (bf16_t*)B)
+    if (incoming && mask) K1_BF16(true, true);
+    else if (incoming) K1_BF16(true, false);
+    else if (mask) K1_BF16(false, true);
+    else K1_BF16(false, false);
+#undef K1_BF16
     return hipGetLastError();
 }
 
