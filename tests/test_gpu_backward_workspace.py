@@ -33,7 +33,7 @@ def test_no_size_needs_more_than_the_unit_block_layout():
 
 
 @pytest.mark.parametrize("saved", [False, True])
-@pytest.mark.parametrize("N", [1, 33, 257])   # the four weights' partials outgrow dA, dB and dx_g up to N = 200, not at 257
+@pytest.mark.parametrize("N", [1, 33, 257])   # the four weights' partials outgrow dA, dB and dx_g up to N = 201, not at 257
 def test_exact_workspace_is_enough(N, saved):
     say(f"backward with its exact workspace N={N} saved={saved}")
     layer, _ = make_layer("bf16", affine=True)
